@@ -55,8 +55,10 @@ _CSRC = os.path.join(ROOT, "paper_2007_07347_amd", "csrc")
 KERNEL_SOURCES = {
     "k_step_tiled": ("step_tiled.hip", "step_common.h"),
     "k_step_batch": ("step_tiled.hip", "step_common.h"),
-    "k_step_cart": ("step_cart.hip", "step_common.h"),
-    "k_step_batch_cart": ("step_cart.hip", "step_common.h"),
+    "k_step_cart": ("step_cart.hip", "cart_math.h", "step_common.h"),
+    "k_step_batch_cart": ("step_cart.hip", "cart_math.h", "step_common.h"),
+    "k_step_block": ("step_block.hip", "cart_math.h", "step_common.h"),
+    "k_step_batch_block": ("step_block.hip", "cart_math.h", "step_common.h"),
 }
 TRAFFIC = os.path.join(ROOT, "profiles", "traffic.json")
 SECTIONS = ("cavity256", "converge", "serving", "cylinder200k", "original", "large",

@@ -29,8 +29,9 @@
  *  - Threads: one handle must not be used by two threads at once.
  *  - Step forms: the fused step (one kernel per time step over tiles of at
  *    most 64 cells of triangles and quads) and, on tensor-product quad meshes,
- *    the structured step run every precision form, both schemes and the
- *    batched calls.  Meshes with polygons of more than four faces (or more
+ *    the structured step (waves marching along strips of the mesh, one launch
+ *    per step, or on small meshes boxes of cells that take several steps per
+ *    launch) run every precision form, both schemes and the batched calls.  Meshes with polygons of more than four faces (or more
  *    than 64 boundary-condition entries, or tile_cells = -1) take the
  *    two-kernel step instead, which is limited: FP64 only, the simplified
  *    scheme only, no batching (SDUGKS_EINVAL otherwise), and it writes fbar+
@@ -133,9 +134,8 @@ typedef struct {
                                      rectangles of two coordinate arrays; periodic sides glued row to row
                                      or column to column; at most 2^29 - 4096 cells): 0 = used when the
                                      mesh is one and tile_cells is 0, 1 = never, 2 = required
-                                     (SDUGKS_EINVAL otherwise).  It fixes
-                                     its own tiles (16 x 14 cells on 512 threads for FP32DEV, 16 x 7 cells on
-                                     256 threads otherwise) and ignores block_threads */
+                                     (SDUGKS_EINVAL otherwise).  It cuts the
+                                     mesh by its size and ignores block_threads */
 } sdugks_params;
 
 typedef struct sdugks_s sdugks_t;
@@ -153,7 +153,8 @@ int sdugks_geometry(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, 
  * size used (0 when the two-kernel step is used: polygons with more than four
  * faces, or tile_cells = -1); n_tiles; max_local: largest tile plus both halo
  * rings; max_ring1: largest tile plus its first ring; structured: 1 when the
- * structured step is used (its tiles are 16 x 14 cells for FP32DEV, 16 x 7 otherwise).  Outputs
+ * structured step is used (the other values then describe nominal tiles of 16 x 14
+ * cells for FP32DEV, 16 x 7 otherwise, not how the step cuts the mesh).  Outputs
  * may be NULL. */
 int sdugks_tiling(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, const sdugks_params *prm,
                   int32_t *tile_cells, int32_t *n_tiles, int32_t *max_local, int32_t *max_ring1,
@@ -172,10 +173,12 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
                   void *stream, void *workspace, size_t workspace_bytes, sdugks_t **out);
 
 /* Advance n >= 0 time steps (asynchronous).  Fails with SDUGKS_EDIVERGED once a
- * residual, mass or state call has seen a non-finite value.  Pairs of steps
- * are replayed from hipGraphs built on first use (32 steps per replay, then
- * 2; an odd last step is launched alone), node by node rather than by stream
- * capture, and launched on the handle's stream, which may be the null stream.
+ * residual, mass or state call has seen a non-finite value.  Pairs of launches
+ * (one step each, several on small structured meshes) are replayed from
+ * hipGraphs built on first use (32 launches per replay, then 2; what is left is
+ * launched alone), node by node rather than by stream capture, and launched on
+ * the handle's stream, which may be the null stream.  A structured mesh that
+ * fits one box of cells takes up to 1000 steps per launch and no graph.
  * Results are bitwise those of sdugks_step_eager. */
 int sdugks_step(sdugks_t *h, int64_t n);
 
@@ -244,16 +247,16 @@ int sdugks_destroy(sdugks_t *h);
 const char *sdugks_last_error(void);
 
 /* ---- batched form: many independent instances (uneven meshes, their own tau,
- * dt and boundary tables) advanced by one launch per step over the tiles of
- * all members; members with three-slot and four-slot cells, or with the two
- * storage forms, go to separate launches.  Each XCD takes an equal,
- * contiguous share of the concatenated tile sequence.  Steps are replayed
- * from hipGraphs built node by node (one of 32 steps, one of 2 for the rest;
- * no stream capture, so other threads may allocate meanwhile) that read
- * a device-side table (members, and each tile slot's member and local tile),
- * so changing the membership only rewrites the table unless the tile count
- * or the LDS a member needs outgrows what the launch was built with (it is
- * then rebuilt).
+ * dt and boundary tables) advanced together over the tiles of all members;
+ * members with three-slot and four-slot cells, of different storage forms, or
+ * on the general and the structured step go to separate launches.  Each XCD
+ * takes an equal, contiguous share of the concatenated tile sequence.  Steps
+ * are replayed from hipGraphs built node by node (2, 4, .. 32 steps; no stream
+ * capture, so other threads may allocate meanwhile) that read a device-side
+ * table (members, and each tile slot's member and local tile), so changing the
+ * membership only rewrites the table unless the tile count or the LDS a member
+ * needs outgrows what the launch was built with, or another cut of the
+ * structured members into work is the better one (it is then rebuilt).
  *  - members: handles using the fused step (n >= 1, no duplicates, same
  *    device); they keep their own state and stay usable individually, and the
  *    batch does not own them: destroy the batch (or change its membership)
@@ -271,8 +274,10 @@ int sdugks_batch_create(sdugks_t *const *members, int32_t n, void *stream, sdugk
  * then return SDUGKS_EINVAL until a later sdugks_batch_set_members succeeds.
  * The same holds for the table refresh inside sdugks_batch_step. */
 int sdugks_batch_set_members(sdugks_batch_t *b, sdugks_t *const *members, int32_t n);
-/* Advance every member n >= 0 time steps (asynchronous on the batch stream),
- * one launch per step and step form (structured or general, precision).
+/* Advance every member n >= 0 time steps (asynchronous on the batch stream):
+ * per step form (structured or general, precision) a chain of launches of its
+ * own, one per step, or of several steps each where all structured members of a
+ * precision are small.
  * Pairs of steps are replayed from hipGraphs of 2, 4, 8, 16 and 32 steps,
  * all built at the first call that needs one (again after a membership
  * change that rebuilds the launch): one graph per set bit of the pairs

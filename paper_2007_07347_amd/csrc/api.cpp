@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/sdugks.h"
+#include "cart_plan.h"
 #include "device.h"
 #include "mesh.h"
 
@@ -131,6 +132,9 @@ struct sdugks_s {
     DevTiles dt{};
     DevCart dc{};
     DevBnd bq{};
+    CartBlock blk{};             // boxes of the form with several steps per launch
+    int kmax = 1;                // steps a launch takes at most (1: the marching or general step)
+    bool whole = false;          // one box holds the mesh
     double *host4 = nullptr;     // pinned, 4 doubles
     // steps replayed from graphs: [buffer index at launch][one pair,
     // kGraphPairs pairs], launched on `stream`
@@ -153,10 +157,15 @@ struct sdugks_s {
     DevScratch scratch() const { return {at<double>(L.off_fbp), at<double>(L.off_sg)}; }
 };
 
-// Members of one launch: same face class (three or four slots) and precision mode.
+// Members of one launch: same face class (three or four slots) and precision
+// mode on the general step; on the structured step the march, or boxes of
+// `block` threads that take K steps per launch (those that wrap rows inside a
+// box apart).
+enum StepForm { kGeneral, kMarch, kBoxes, kBoxesWrap };
 struct BatchGroup {
     int D = 4, mode = 0, block = 64;
-    bool cart = false;
+    StepForm form = kGeneral;
+    CartPlan plan;
     size_t lds = 0;
     int n_inst = 0, n_tiles = 0, cap_inst = 0, cap_tiles = 0;
     BatchInst *d_inst = nullptr;      // device table, capacity cap_inst
@@ -228,6 +237,14 @@ int upload_rows(T *dst, const std::vector<T> &src, size_t rows, size_t nc, size_
     return SDUGKS_OK;
 }
 
+// Factor of the face distribution f_face = fc1 (fbar + fb feq): 2 tau / (2 tau + h)
+// with h the step (the paper's scheme) or half of it (the original one).
+double face_factor(const MeshBuild &mb, int scheme)
+{
+    const double hh = scheme == SDUGKS_SCHEME_ORIGINAL ? 0.5 * mb.dt : mb.dt;
+    return 2.0 * mb.tau / (2.0 * mb.tau + hh);
+}
+
 double feq_host(int i, double rho, double ux, double uy)
 {
     static const double ex[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1}, ey[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
@@ -258,11 +275,13 @@ int reduce(sdugks_t *h, int update_snap, double out[4])
 
 // One step that reads buffer index c, on stream st, or appended to a graph
 // chain (no bookkeeping).
-int launch_step_at(sdugks_t *h, int c, hipStream_t st, GraphChain *gc = nullptr)
+int launch_step_at(sdugks_t *h, int c, hipStream_t st, GraphChain *gc = nullptr, int steps = 1)
 {
     DevState s = h->state_at(c);
     const int lagged = h->macro == SDUGKS_MACRO_LAGGED;
-    if (h->mb.cart) {
+    if (h->blk.threads) {
+        HIPCHK(launch_step_block(h->dm, h->dc, s, h->blk, lagged, h->precision, steps, st, gc));
+    } else if (h->mb.cart) {
         HIPCHK(launch_step_cart(h->dm, h->dc, s, lagged, h->precision, st, gc));
     } else if (h->mb.n_tiles > 0) {
         HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, st, gc));
@@ -274,12 +293,12 @@ int launch_step_at(sdugks_t *h, int c, hipStream_t st, GraphChain *gc = nullptr)
     return SDUGKS_OK;
 }
 
-int enqueue_step(sdugks_t *h)
+int enqueue_step(sdugks_t *h, int steps = 1)
 {
-    int rc = launch_step_at(h, h->cur, h->stream);
+    int rc = launch_step_at(h, h->cur, h->stream, nullptr, steps);
     if (rc) return rc;
     h->cur ^= 1;
-    h->step++;
+    h->step += steps;
     return SDUGKS_OK;
 }
 
@@ -305,8 +324,8 @@ int capture_step_graph(sdugks_t *h, int c, int64_t pairs, hipGraph_t &graph, hip
     gc.graph = gr;
     int rc = 0;
     for (int64_t k = 0; k < pairs && !rc; k++) {
-        rc = launch_step_at(h, c, h->stream, &gc);
-        if (!rc) rc = launch_step_at(h, c ^ 1, h->stream, &gc);
+        rc = launch_step_at(h, c, h->stream, &gc, h->kmax);
+        if (!rc) rc = launch_step_at(h, c ^ 1, h->stream, &gc, h->kmax);
     }
     if (rc) { (void)hipGraphDestroy(gr); return rc; }
     const hipError_t ie = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
@@ -497,17 +516,35 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         h->bq.sum = h->at<double>(L.off_bq_sum);
     }
     if (mb.cart) {
+        const double c1 = face_factor(mb, h->scheme);
+        std::vector<CartRow<float>> row32;
+        std::vector<CartRow<double>> row64;
+        for (int32_t j = 0; j < mb.ny; j++) {
+            const double *r = &mb.row[(size_t)j * kCartVals];
+            if (h->precision == SDUGKS_FP32DEV)
+                row32.push_back({(float)r[1], (float)r[2], (float)r[3], (float)r[4], (float)r[0] * (float)c1, r[5]});
+            else row64.push_back({r[1], r[2], r[3], r[4], r[0] * c1, r[5]});
+        }
+        const void *rows = row32.empty() ? (const void *)row64.data() : (const void *)row32.data();
+        const size_t row_bytes = row32.size() * sizeof(CartRow<float>) + row64.size() * sizeof(CartRow<double>);
         auto up = [&](size_t off, const void *src, size_t bytes) {
             return hipMemcpy(h->base + off, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
         };
         if (!up(L.off_ccol, mb.col.data(), mb.col.size() * sizeof(double)) ||
-            !up(L.off_crow, mb.row.data(), mb.row.size() * sizeof(double)) ||
+            !up(L.off_crow, rows, row_bytes) ||
             !up(L.off_cside, mb.side.data(), mb.side.size() * sizeof(int32_t)))
             return cleanup(fail(SDUGKS_EHIP, "upload of the structured-grid tables failed"));
-        h->dc.nx = mb.nx; h->dc.ny = mb.ny; h->dc.ntx = mb.ntx; h->dc.nty = mb.nty;
+        h->dc.nx = mb.nx; h->dc.ny = mb.ny;
         h->dc.per_x = mb.per_x; h->dc.per_y = mb.per_y;
+        const CartPlan plan = plan_cart({h->dc}, h->precision);
+        cart_cut(h->dc, plan.rows);
+        if (plan.threads) {
+            h->blk = cart_block(h->dc, plan.threads, plan.K);
+            h->whole = h->blk.nbx * h->blk.nby == 1;
+            h->kmax = h->whole ? kWholeSteps : plan.K;
+        }
         h->dc.col = h->at<double>(L.off_ccol);
-        h->dc.row = h->at<double>(L.off_crow);
+        h->dc.row = h->at<void>(L.off_crow);
         h->dc.side = h->at<int32_t>(L.off_cside);
     } else if (tiled) {
         auto up = [&](size_t off, const void *src, size_t bytes) {
@@ -770,23 +807,33 @@ int sdugks_step(sdugks_t *h, int64_t n)
     if (n < 0) return fail(SDUGKS_EINVAL, "negative step count");
     if (h->diverged) return fail(SDUGKS_EDIVERGED, "state is not finite; reset it with sdugks_set_state");
     HIPCHK(hipSetDevice(h->device));
-    // whole runs of kGraphPairs pairs replay the long graph, the remaining
-    // pairs the one-pair graph, an odd last step is launched alone
-    int64_t pairs = n / 2;
-    const int64_t runs = pairs / kGraphPairs;
-    pairs -= runs * kGraphPairs;
-    const int c = h->cur;
+    // whole runs of kGraphPairs pairs of launches (of kmax steps each) replay
+    // the long graph, the remaining pairs the one-pair graph, what is left (less
+    // than two launches) is launched alone; a mesh in one box takes all steps in
+    // one launch
     int rc;
-    if (runs > 0) {
-        if (!h->exec[c][1] && (rc = capture_step_graph(h, c, kGraphPairs, h->graph[c][1], h->exec[c][1]))) return rc;
-        for (int64_t k = 0; k < runs; k++) HIPCHK(hipGraphLaunch(h->exec[c][1], h->stream));
+    if (!h->whole) {
+        int64_t pairs = n / (2 * h->kmax);
+        const int64_t runs = pairs / kGraphPairs;
+        pairs -= runs * kGraphPairs;
+        const int c = h->cur;
+        if (runs > 0) {
+            if (!h->exec[c][1] && (rc = capture_step_graph(h, c, kGraphPairs, h->graph[c][1], h->exec[c][1]))) return rc;
+            for (int64_t k = 0; k < runs; k++) HIPCHK(hipGraphLaunch(h->exec[c][1], h->stream));
+        }
+        if (pairs > 0) {
+            if (!h->exec[c][0] && (rc = capture_step_graph(h, c, 1, h->graph[c][0], h->exec[c][0]))) return rc;
+            for (int64_t k = 0; k < pairs; k++) HIPCHK(hipGraphLaunch(h->exec[c][0], h->stream));
+        }
+        const int64_t done = n / (2 * h->kmax) * (2 * h->kmax);
+        h->step += done;
+        n -= done;
     }
-    if (pairs > 0) {
-        if (!h->exec[c][0] && (rc = capture_step_graph(h, c, 1, h->graph[c][0], h->exec[c][0]))) return rc;
-        for (int64_t k = 0; k < pairs; k++) HIPCHK(hipGraphLaunch(h->exec[c][0], h->stream));
+    while (n > 0) {
+        const int k = (int)std::min<int64_t>(n, h->kmax);
+        if ((rc = enqueue_step(h, k))) return rc;
+        n -= k;
     }
-    h->step += 2 * (n / 2);
-    if (n & 1) return enqueue_step(h);
     return SDUGKS_OK;
 }
 
@@ -823,7 +870,8 @@ int sdugks_step_profiled(sdugks_t *h, int64_t n, double *avg_ms, const char **na
         const int lagged = h->macro == SDUGKS_MACRO_LAGGED;
         HIPCHK(hipEventRecord(ev[0], h->stream));
         if (h->mb.cart) {
-            HIPCHK(launch_step_cart(h->dm, h->dc, s, lagged, h->precision, h->stream));
+            int rc = launch_step_at(h, h->cur, h->stream);
+            if (rc) return rc;
             HIPCHK(hipEventRecord(ev[1], h->stream));
         } else if (tiled) {
             HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, h->stream));
@@ -953,31 +1001,68 @@ void batch_release_groups(sdugks_batch_t *b)
     b->groups.clear();
 }
 
+// Workgroups a member takes in a launch of its group.
+int32_t member_tiles(const sdugks_t *h, const BatchGroup &g)
+{
+    if (g.form == kGeneral) return h->mb.n_tiles;
+    if (g.form == kMarch) {
+        DevCart c = h->dc;
+        cart_cut(c, g.plan.rows);
+        return cart_groups(c);
+    }
+    const CartBlock b = cart_block(h->dc, g.plan.threads, g.plan.K);
+    return b.nbx * b.nby;
+}
+
 // (Re)build the device tables for the current members.  Existing tables and
 // the captured graph are kept when every group still fits their capacity,
 // launch shape and LDS; otherwise they are reallocated and the graph dropped.
 int batch_build_tables(sdugks_batch_t *b)
 {
+    // one plan for the structured members of each precision
+    CartPlan plans[3];
+    for (int mode = 0; mode < 3; mode++) {
+        std::vector<DevCart> cs;
+        for (sdugks_t *h : b->members)
+            if (h->mb.cart && h->precision == mode) cs.push_back(h->dc);
+        if (!cs.empty()) plans[mode] = plan_cart(cs, mode);
+    }
     std::vector<BatchGroup> want;
     for (size_t k = 0; k < b->members.size(); k++) {
         sdugks_t *h = b->members[k];
         const int D = h->mb.D <= 3 ? 3 : 4, mode = h->precision;
-        const bool cart = h->mb.cart;
+        const CartPlan &plan = plans[mode];
+        StepForm form = h->mb.cart ? kMarch : kGeneral;
+        if (form == kMarch && plan.threads)
+            form = block_wraps(h->dc, cart_block(h->dc, plan.threads, plan.K)) ? kBoxesWrap : kBoxes;
         BatchGroup *g = nullptr;
-        for (auto &x : want) if (x.D == D && x.mode == mode && x.cart == cart) g = &x;
-        if (!g) { want.emplace_back(); g = &want.back(); g->D = D; g->mode = mode; g->cart = cart; }
+        for (auto &x : want) if (x.D == D && x.mode == mode && x.form == form) g = &x;
+        if (!g) {
+            want.emplace_back();
+            g = &want.back();
+            g->D = D; g->mode = mode; g->form = form;
+            if (form != kGeneral) g->plan = plan;
+        }
         g->members.push_back((int)k);
-        g->block = cart ? step_cart_threads(mode) : std::max(g->block, h->block);
-        g->lds = std::max(g->lds, cart ? step_cart_lds_bytes(mode, (int)h->mb.bcs.size())
-                                       : step_tiled_lds_bytes(h->dt, mode, (int)h->mb.bcs.size()));
+        const int n_bc = (int)h->mb.bcs.size();
+        size_t lds = march_lds_bytes(n_bc);
+        if (form == kGeneral) {
+            g->block = std::max(g->block, h->block);
+            lds = step_tiled_lds_bytes(h->dt, mode, n_bc);
+        } else if (form != kMarch) {
+            g->block = plan.threads;
+            lds = step_block_lds_bytes(plan.threads, mode, n_bc);
+        }
+        g->lds = std::max(g->lds, lds);
         g->n_inst++;
-        g->n_tiles += h->mb.n_tiles;
+        g->n_tiles += member_tiles(h, *g);
     }
     bool reuse = want.size() == b->groups.size();
     for (size_t k = 0; reuse && k < want.size(); k++) {
         const BatchGroup &o = b->groups[k], &n = want[k];
-        reuse = o.D == n.D && o.mode == n.mode && o.cart == n.cart && o.block >= n.block && o.lds >= n.lds &&
-                o.cap_inst >= n.n_inst && o.cap_tiles >= n.n_tiles;
+        reuse = o.D == n.D && o.mode == n.mode && o.form == n.form && o.lds >= n.lds && o.cap_inst >= n.n_inst &&
+                o.cap_tiles >= n.n_tiles &&
+                (n.form == kGeneral ? o.block >= n.block : o.block == n.block && o.plan.K == n.plan.K);
     }
     if (!reuse) {
         batch_release_graph(b);
@@ -1006,6 +1091,7 @@ int batch_build_tables(sdugks_batch_t *b)
     } else {
         for (size_t k = 0; k < want.size(); k++) {
             b->groups[k].members = want[k].members;
+            b->groups[k].plan = want[k].plan;
             b->groups[k].n_inst = want[k].n_inst;
             b->groups[k].n_tiles = want[k].n_tiles;
         }
@@ -1023,6 +1109,8 @@ int batch_build_tables(sdugks_batch_t *b)
             e.m = h->dm;
             e.t = h->dt;
             e.c = h->dc;
+            if (g.form == kMarch) cart_cut(e.c, g.plan.rows);
+            else if (g.form != kGeneral) e.b = cart_block(h->dc, g.plan.threads, g.plan.K);
             for (int p = 0; p < 2; p++) {
                 e.f[p] = h->base + h->L.off_f[p];
                 e.W[p] = h->at<double>(h->L.off_W[p]);
@@ -1030,7 +1118,7 @@ int batch_build_tables(sdugks_batch_t *b)
             }
             e.parity0 = h->cur;
             e.lagged = h->macro == SDUGKS_MACRO_LAGGED;
-            for (int32_t t = 0; t < h->mb.n_tiles; t++) seq.push_back(make_int2(k, t));
+            for (int32_t t = 0, n = member_tiles(h, g); t < n; t++) seq.push_back(make_int2(k, t));
         }
         // each XCD's range of tile slots gets an equal, contiguous share of the
         // live tiles at its start; the remaining slots are empty (-1)
@@ -1065,19 +1153,15 @@ int batch_build(sdugks_batch_t *b)
     return rc;
 }
 
-// One batched step: a launch per group.  In a graph the groups' nodes of one
-// step depend only on the previous step's nodes (their members are disjoint),
-// so the runtime may run them side by side.
-int batch_launch(sdugks_batch_t *b, int parity, GraphChain *gc = nullptr)
+// `steps` steps of one group (boxes: at most K of them; else one).
+hipError_t batch_launch(sdugks_batch_t *b, const BatchGroup &g, int steps, int parity, GraphChain *gc = nullptr)
 {
-    if (gc) gc->begin_fan();
-    for (auto &g : b->groups) {
-        BatchTable tab{g.d_inst, g.d_tmap};
-        if (g.cart) HIPCHK(launch_step_batch_cart(tab, g.mode, parity, g.cap_tiles, g.lds, b->stream, gc));
-        else HIPCHK(launch_step_batch(tab, g.D, g.mode, parity, g.cap_tiles, g.lds, g.block, b->stream, gc));
-    }
-    if (gc) gc->end_fan();
-    return SDUGKS_OK;
+    const BatchTable tab{g.d_inst, g.d_tmap};
+    if (g.form == kGeneral)
+        return launch_step_batch(tab, g.D, g.mode, parity, g.cap_tiles, g.lds, g.block, b->stream, gc);
+    if (g.form == kMarch) return launch_step_batch_cart(tab, g.mode, parity, g.cap_tiles, g.lds, b->stream, gc);
+    return launch_step_batch_block(tab, g.form == kBoxesWrap, g.block, g.mode, steps, parity, g.cap_tiles, g.lds,
+                                   b->stream, gc);
 }
 
 // Order the batch stream after the members' streams (before) or the members'
@@ -1158,19 +1242,26 @@ int sdugks_batch_set_members(sdugks_batch_t *b, sdugks_t *const *members, int32_
 
 namespace {
 
-// `pairs` pairs of batched steps as one graph, built node by node.
+// `pairs` pairs of batched steps as one graph, built node by node: each
+// group a chain of its own (their members are disjoint, so the runtime may run
+// the chains side by side), with an even number of launches, so that every
+// member's buffer index ends where it began.
 int batch_capture(sdugks_batch_t *b, int64_t pairs, hipGraph_t &graph, hipGraphExec_t &exec)
 {
     hipGraph_t gr = nullptr;
     HIPCHK(hipGraphCreate(&gr, 0));
-    GraphChain gc;
-    gc.graph = gr;
-    int rc = 0;
-    for (int64_t k = 0; k < pairs && !rc; k++) {
-        rc = batch_launch(b, 0, &gc);
-        if (!rc) rc = batch_launch(b, 1, &gc);
+    for (const BatchGroup &g : b->groups) {
+        GraphChain gc;
+        gc.graph = gr;
+        const int64_t steps = 2 * pairs, K = std::max(1, g.plan.K), launches = 2 * ((pairs + K - 1) / K);
+        hipError_t e = hipSuccess;
+        for (int64_t k = 0; k < launches && e == hipSuccess; k++)
+            e = batch_launch(b, g, (int)(steps * (k + 1) / launches - steps * k / launches), (int)(k & 1), &gc);
+        if (e != hipSuccess) {
+            (void)hipGraphDestroy(gr);
+            return fail(SDUGKS_EHIP, std::string("batch graph: ") + hipGetErrorString(e));
+        }
     }
-    if (rc) { (void)hipGraphDestroy(gr); return rc; }
     const hipError_t ie = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
     if (ie != hipSuccess) {
         (void)hipGraphDestroy(gr);
@@ -1216,8 +1307,7 @@ int sdugks_batch_step(sdugks_batch_t *b, int64_t n)
         if (pairs & ((int64_t)1 << k)) HIPCHK(hipGraphLaunch(b->exec[k], b->stream));
     for (int64_t k = 0; k < runs; k++) HIPCHK(hipGraphLaunch(b->exec[kBatchGraphs - 1], b->stream));
     if (n & 1) {
-        rc = batch_launch(b, 0);
-        if (rc) return rc;
+        for (const BatchGroup &g : b->groups) HIPCHK(batch_launch(b, g, 1, 0));
     }
     rc = batch_join(b, false);
     if (rc) return rc;

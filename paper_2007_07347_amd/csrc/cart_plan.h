@@ -1,0 +1,130 @@
+// How structured instances are cut into work (host only): strips and segments
+// of the marching step, or boxes of the form with several steps per launch, and
+// which of the two takes a step sooner.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+#include "device.h"
+#include "mesh.h"
+
+namespace sdg {
+
+// Times in us that the choice rests on, measured on this chip (256 CUs of four
+// SIMDs): a launch, from the end of the one before it to its first result, and
+// a row of the march or a step of the boxes with one wave and with two waves
+// on every SIMD (the registers allow no third).
+struct CartTimes {
+    double launch, row1, row2, round, step1, step2;
+};
+inline CartTimes cart_times(int precision)
+{
+    if (precision == SDUGKS_FP32DEV) return {2.5, 1.7, 2.35, 1.2, 1.9, 2.5};
+    return {2.5, 1.8, 2.6, 1.2, 2.0, 3.3};
+}
+constexpr int64_t kSimds = 1024;
+constexpr int32_t kWholeSteps = 1000;   // steps per launch of a mesh in one box, at most
+
+// `units` equal waves, two at a time on a SIMD: time per unit of their length.
+inline double cart_rounds(int64_t waves, double one, double two)
+{
+    const int64_t full = waves / (2 * kSimds), rest = waves % (2 * kSimds);
+    return (double)full * two + (rest > kSimds ? two : (rest > 0 ? one : 0.0));
+}
+
+struct CartPlan {
+    int32_t rows = 0;                   // the march: rows of a segment, at most
+    int32_t threads = 0, K = 0;         // boxes: threads per box, steps per launch (0: the march)
+    double us = 0.0;                    // time per step
+};
+
+inline void cart_cut(DevCart &c, int32_t rows)
+{
+    c.strips = (c.nx + kCartCols - 1) / kCartCols;
+    c.strip_w = c.nx / c.strips;
+    c.strip_more = c.nx % c.strips;
+    c.segs = (c.ny + rows - 1) / rows;
+    c.seg_h = c.ny / c.segs;
+    c.seg_more = c.ny % c.segs;
+    c.inv_segs = (uint32_t)std::min<uint64_t>(((uint64_t)1 << 32) / (uint64_t)c.segs, UINT32_MAX);
+}
+
+// The march over all members: segments of nearly `rows` rows each, such that
+// the waves fill the SIMDs in whole rounds and are not much longer than their
+// start (about three rows' time: the two rows before and after a segment take
+// part of a row's work).  Long segments read few rows twice.
+inline CartPlan plan_march(const std::vector<DevCart> &members, int precision)
+{
+    const CartTimes t = cart_times(precision);
+    CartPlan best;
+    for (int32_t rows = 1; rows <= 64; rows++) {
+        int64_t waves = 0;
+        int32_t longest = 0;
+        for (const DevCart &m : members) {
+            DevCart c = m;
+            cart_cut(c, rows);
+            waves += (int64_t)c.strips * c.segs;
+            longest = std::max(longest, (c.ny + c.segs - 1) / c.segs);
+        }
+        const double us = t.launch + (longest + 3.0) * cart_rounds(waves, t.row1, t.row2);
+        if (best.rows == 0 || us < best.us) best = {rows, 0, 0, us};
+    }
+    return best;
+}
+
+// Boxes of n cells along an axis, B cells each, after K steps, with `pad` ghost
+// cells at a wall (0: boxes too small).
+inline int32_t cart_boxes(int32_t n, bool per, int32_t B, int32_t pad, int32_t K)
+{
+    if (per ? n <= B : n + 2 * pad <= B) return 1;
+    const int32_t T = B - 4 * K, first = B - pad - 2 * K;
+    if (T < 1) return 0;
+    if (per) return (n + T - 1) / T;
+    return n <= 2 * first ? 2 : 2 + (n - 2 * first + T - 1) / T;
+}
+
+// The box shape with the fewest boxes for an instance (threads 0: none fits).
+inline CartBlock cart_block(const DevCart &c, int32_t threads, int32_t K)
+{
+    CartBlock best{};
+    int64_t fewest = 0;
+    for (int32_t lb = 2; lb <= 6; lb++) {
+        const int32_t by = threads >> lb;
+        if (by < 1) break;
+        const int64_t x = cart_boxes(c.nx, c.per_x, 1 << lb, 1, K), y = cart_boxes(c.ny, c.per_y, by, 0, K);
+        if (x * y == 0 || x * y > (1 << 20)) continue;
+        if (best.threads == 0 || x * y < fewest) {
+            best = {lb, threads, K, (int32_t)x, (int32_t)y};
+            fewest = x * y;
+        }
+    }
+    return best;
+}
+
+// Boxes over all members, or the march where that takes less time.
+inline CartPlan plan_cart(const std::vector<DevCart> &members, int precision)
+{
+    const CartTimes t = cart_times(precision);
+    CartPlan best = plan_march(members, precision);
+    for (int32_t threads : {64, 128, 256, 512})
+        for (int32_t K : {1, 2, 3, 4, 5, 6, 32}) {      // 32: only where every mesh fits one box
+            int64_t boxes = 0;
+            bool fits = true;
+            for (const DevCart &m : members) {
+                const CartBlock b = cart_block(m, threads, K);
+                if (b.threads == 0) { fits = false; break; }
+                boxes += (int64_t)b.nbx * b.nby;
+            }
+            if (!fits) continue;
+            // a workgroup of four or eight waves takes one or two on each of a CU's SIMDs
+            const int64_t waves = boxes * (threads / 64);
+            const int64_t slots = threads == 512 ? (boxes + 255) / 256 * 256 * 8 : waves;
+            const double us = (t.launch + cart_rounds(slots, t.round + K * t.step1, t.round + K * t.step2)) / K;
+            if (us < best.us) best = {best.rows, threads, K, us};
+        }
+    return best;
+}
+
+}  // namespace sdg

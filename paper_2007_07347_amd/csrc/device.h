@@ -5,8 +5,9 @@
 
 #include <cstdint>
 #include <tuple>
-#include <vector>
 #include <utility>
+
+#include "mesh.h"
 
 namespace sdg {
 
@@ -63,14 +64,34 @@ struct DevTiles {
     const float2 *fr32, *lw32;          // deviation form
 };
 
-// Structured step (tensor-product quad meshes): grid and tile counts,
-// periodic flags, per-column / per-row records [n][kCartVals] and the
-// boundary-condition entry of every boundary face of the four sides (bottom
-// [nx], top [nx], left [ny], right [ny]; -1 on periodic sides).
+// Structured step (tensor-product quad meshes): grid, periodic flags, how the
+// march cuts it (strips of columns, segments of rows: so many of one cell more
+// than the rest), per-column and per-row records and the boundary-condition
+// entry of every boundary face of the four sides (bottom [nx], top [nx], left
+// [ny], right [ny]; -1 on periodic sides).
 struct DevCart {
-    int32_t nx, ny, ntx, nty, per_x, per_y;
-    const double *col, *row;
+    int32_t nx, ny, per_x, per_y;
+    int32_t strips, strip_w, strip_more, segs, seg_h, seg_more;
+    uint32_t inv_segs;                  // 2^32 / segs, rounded down
+    const double *col;                  // [nx][kCartVals]
+    const void *row;                    // [ny] CartRow of the step's arithmetic
     const int32_t *side;
+};
+
+// A row's record in the step's arithmetic: offsets of its lower and upper face
+// from its centre, least-squares weights of the points below and above, height
+// times the factor of the face distribution, 1 / height.
+template <typename R>
+struct CartRow {
+    R hb, ht, wb, wt, c;
+    double ih;
+};
+
+// Boxes of the structured step's form with several steps per launch: box
+// columns (a power of two up to 64) and threads (one per box cell), steps K
+// after which a box that does not hold the whole axis is spent, boxes per axis.
+struct CartBlock {
+    int32_t log_bx, threads, K, nbx, nby;
 };
 
 // One member of a batched launch: its mesh, tiles (or structured grid), both
@@ -79,6 +100,7 @@ struct BatchInst {
     DevMesh m;
     DevTiles t;
     DevCart c;
+    CartBlock b;
     void *f[2];
     double *W[2];
     double *G[2];
@@ -119,22 +141,9 @@ struct DevScratch {
 // previous one).  Graphs are built node by node rather than by stream
 // capture, so that another thread's allocations or synchronous copies can
 // never invalidate them.
-// Kernel nodes appended to a graph.  A node depends on `deps` (the previous
-// node, or every node of the previous fan); between begin_fan and end_fan the
-// nodes are collected instead, all depending on the same `deps`, so they may
-// run concurrently, and end_fan makes the next node wait for all of them.
 struct GraphChain {
     hipGraph_t graph = nullptr;
-    std::vector<hipGraphNode_t> deps;
-    std::vector<hipGraphNode_t> fan;
-    bool fanning = false;
-    void begin_fan() { fan.clear(); fanning = true; }
-    void end_fan()
-    {
-        fanning = false;
-        if (!fan.empty()) deps.swap(fan);
-        fan.clear();
-    }
+    hipGraphNode_t last = nullptr;
 };
 
 template <typename Tup, size_t... I>
@@ -160,11 +169,8 @@ inline hipError_t emit(void (*fn)(P...), dim3 grid, dim3 blk, size_t lds, hipStr
     kp.kernelParams = ptrs;
     kp.extra = nullptr;
     hipGraphNode_t node = nullptr;
-    const hipError_t e = hipGraphAddKernelNode(&node, gc->graph, gc->deps.empty() ? nullptr : gc->deps.data(),
-                                               gc->deps.size(), &kp);
-    if (e != hipSuccess) return e;
-    if (gc->fanning) gc->fan.push_back(node);
-    else gc->deps.assign(1, node);
+    const hipError_t e = hipGraphAddKernelNode(&node, gc->graph, gc->last ? &gc->last : nullptr, gc->last ? 1 : 0, &kp);
+    if (e == hipSuccess) gc->last = node;
     return e;
 }
 
@@ -185,8 +191,21 @@ size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc);
 // structured step).
 hipError_t launch_step_cart(const DevMesh &m, const DevCart &c, const DevState &s, int lagged, int mode,
                             hipStream_t st, GraphChain *gc = nullptr);
-size_t step_cart_lds_bytes(int mode, int n_bc);
-int step_cart_threads(int mode);
+// The same, `steps` steps at once (at most B.K unless one box holds the mesh).
+hipError_t launch_step_block(const DevMesh &m, const DevCart &c, const DevState &s, const CartBlock &B, int lagged,
+                             int mode, int steps, hipStream_t st, GraphChain *gc = nullptr);
+size_t step_block_lds_bytes(int threads, int mode, int n_bc);
+inline bool block_wraps(const DevCart &c, const CartBlock &B)
+{
+    return c.per_x && B.nbx == 1 && c.nx <= (1 << B.log_bx);
+}
+// The batched form: members whose boxes have the same number of threads and
+// which all wrap rows inside a box or all do not.
+hipError_t launch_step_batch_block(const BatchTable &tab, bool wrap, int threads, int mode, int steps, int parity,
+                                   int cap_tiles, size_t lds, hipStream_t st, GraphChain *gc = nullptr);
+size_t march_lds_bytes(int n_bc);       // besides the march's static LDS
+// Workgroups of a structured instance cut into strips and segments.
+inline int32_t cart_groups(const DevCart &c) { return c.strips * c.segs; }
 hipError_t launch_step_batch_cart(const BatchTable &tab, int mode, int parity, int cap_tiles, size_t lds,
                                   hipStream_t st, GraphChain *gc = nullptr);
 // Batched fused step over the tiles of all members (same D class and mode).

@@ -529,7 +529,7 @@ int build_mesh(const sdugks_mesh *m, const sdugks_bc *bc, int32_t n_bc, const sd
     std::vector<std::pair<size_t, size_t>> parts;
     if (cart) {
         for (int32_t j = 0; j < cny; j++)
-            for (int32_t i = 0; i < cnx; i++) perm[cart_index(i, j, cnx, cny)] = cart_cell[i + (size_t)cnx * j];
+            for (int32_t i = 0; i < cnx; i++) perm[i + (size_t)cnx * j] = cart_cell[i + (size_t)cnx * j];
     } else if (tiled) {
         for (int32_t c = 0; c < nc; c++) perm[c] = c;
         rcb(perm, 0, nc, ((int64_t)nc + T - 1) / T, cx, cy, parts);
@@ -664,10 +664,8 @@ int build_mesh(const sdugks_mesh *m, const sdugks_bc *bc, int32_t n_bc, const sd
         axis(cys, cny, cper_y, out.row);
         out.nx = cnx; out.ny = cny; out.per_x = cper_x; out.per_y = cper_y;
         const int32_t rows = cart_tile_rows(prm->precision);
-        out.ntx = (cnx + kCartTX - 1) / kCartTX;
-        out.nty = (cny + rows - 1) / rows;
         out.side = cside;
-        out.n_tiles = out.ntx * out.nty;
+        out.n_tiles = (cnx + kCartTX - 1) / kCartTX * ((cny + rows - 1) / rows);
         out.tile_T = kCartTX * rows;
     } else if (tiled) {
         if (!build_tiles(out, parts)) BAD("internal: the two views of a face are not exact mirrors");

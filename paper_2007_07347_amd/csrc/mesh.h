@@ -73,9 +73,7 @@ struct MeshBuild {
     std::vector<double> lw;
     // Structured step (tensor-product quad meshes; cart == true): the cells
     // are (i, j), 0 <= i < nx, 0 <= j < ny, with corners (xs[i], ys[j]) ..
-    // (xs[i+1], ys[j+1]); storage tiles of kCartTX x kCartTY cells in
-    // row-major tile order, cells row-major inside each tile (the internal
-    // order); ntx x nty step tiles of kCartTX x cart_tile_rows(precision).  Per
+    // (xs[i+1], ys[j+1]); the internal order is row by row.  Per
     // column i, col[i][kCartVals]: width, offsets of its left and right face
     // midpoints from its centre, least-squares weights of its left and right
     // stencil points (neighbour centre, periodic image, or the wall face
@@ -83,32 +81,24 @@ struct MeshBuild {
     // entry of every boundary face of the four sides (-1 where periodic):
     // side[0..nx) bottom, [nx..2nx) top, [2nx..2nx+ny) left, then right.
     bool cart = false;
-    int32_t nx = 0, ny = 0, ntx = 0, nty = 0, per_x = 0, per_y = 0;
+    int32_t nx = 0, ny = 0, per_x = 0, per_y = 0;
     std::vector<double> col, row;
     std::vector<int32_t> side;
 };
 
-// Storage tile of the structured step (16 x 14 cells) and the per-column /
-// per-row record length.  The FP32-deviation step works on whole storage
-// tiles; the forms with FP64 face arithmetic on their upper and lower halves
-// (16 x 7), whose cells are contiguous too, so that their LDS (twice the
-// bytes per value) stays small enough for several workgroups per CU.
+// Nominal tiles of the structured step, as sdugks_tiling reports them (a unit of
+// work for callers that size by tiles; the step itself cuts a mesh by its size,
+// cart_plan.h): 16 x 14 cells for FP32 deviations, 16 x 7 otherwise.  Length of a
+// per-column / per-row record.
 constexpr int32_t kCartTX = 16, kCartTY = 14;
 __host__ __device__ constexpr int32_t cart_tile_rows(int precision)
 {
     return precision == SDUGKS_FP32DEV ? kCartTY : kCartTY / 2;
 }
 constexpr int32_t kCartVals = 8;   // width, left offset, right offset, left weight, right weight, 1/width, pad, pad
-// Internal index of cell (i, j) of a structured mesh: tiles in row-major
-// order, each tile's cells in rows; the last tile column and row may be
-// narrower.
-__host__ __device__ inline int32_t cart_index(int32_t i, int32_t j, int32_t nx, int32_t ny)
-{
-    const int32_t tx = i / kCartTX, ty = j / kCartTY;
-    const int32_t h = ny - ty * kCartTY < kCartTY ? ny - ty * kCartTY : kCartTY;
-    const int32_t w = nx - tx * kCartTX < kCartTX ? nx - tx * kCartTX : kCartTX;
-    return ty * kCartTY * nx + tx * kCartTX * h + (j - ty * kCartTY) * w + (i - tx * kCartTX);
-}
+// Columns a wave of the marching step writes: its lanes less two halo columns
+// on either side.
+constexpr int32_t kCartCols = 60;
 
 // Accelerator complex dies of an MI355X, each with its own L2: the fused step
 // gives each a contiguous range of tiles.

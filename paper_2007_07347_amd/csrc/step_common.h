@@ -53,6 +53,22 @@ __device__ __forceinline__ gmem<T> *gout(T *p)
     return (gmem<T> *)p;
 }
 
+// Buffers of a batch member at a launch of the given parity.
+__device__ __forceinline__ DevState batch_state(const BatchInst &in, int parity)
+{
+    const bool sw = ((in.parity0 ^ parity) & 1) != 0;
+    void *const f0 = in.f[0], *const f1 = in.f[1];
+    double *const W0 = in.W[0], *const W1 = in.W[1], *const G0 = in.G[0], *const G1 = in.G[1];
+    DevState s;
+    s.W = sw ? W1 : W0; s.G = sw ? G1 : G0; s.Wo = sw ? W0 : W1; s.Go = sw ? G0 : G1;
+    void *const fi = sw ? f1 : f0, *const fo = sw ? f0 : f1;
+    s.f = reinterpret_cast<const double *>(fi);
+    s.fo = reinterpret_cast<double *>(fo);
+    s.f32 = reinterpret_cast<const float *>(fi);
+    s.fo32 = reinterpret_cast<float *>(fo);
+    return s;
+}
+
 // c x for c in {-1, 0, 1}
 template <int C, typename T>
 __device__ __forceinline__ T cmul(T x)
