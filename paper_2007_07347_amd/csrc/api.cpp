@@ -165,6 +165,7 @@ enum StepForm { kGeneral, kMarch, kBoxes, kBoxesWrap };
 struct BatchGroup {
     int D = 4, mode = 0, block = 64;
     StepForm form = kGeneral;
+    int narrow = 0;
     CartPlan plan;
     size_t lds = 0;
     int n_inst = 0, n_tiles = 0, cap_inst = 0, cap_tiles = 0;
@@ -1019,28 +1020,33 @@ int32_t member_tiles(const sdugks_t *h, const BatchGroup &g)
 // launch shape and LDS; otherwise they are reallocated and the graph dropped.
 int batch_build_tables(sdugks_batch_t *b)
 {
-    // one plan for the structured members of each precision
-    CartPlan plans[3];
-    for (int mode = 0; mode < 3; mode++) {
-        std::vector<DevCart> cs;
-        for (sdugks_t *h : b->members)
-            if (h->mb.cart && h->precision == mode) cs.push_back(h->dc);
-        if (!cs.empty()) plans[mode] = plan_cart(cs, mode);
-    }
+    // one plan for the structured members of each precision, and another for
+    // those that are narrow and periodic (channels a few columns wide): one box
+    // often holds all of such a mesh, which may then take many steps per launch
+    auto narrow = [](const sdugks_t *h) { return h->dc.per_x && h->dc.nx <= 16; };
+    CartPlan plans[3][2];
+    for (int mode = 0; mode < 3; mode++)
+        for (int k = 0; k < 2; k++) {
+            std::vector<DevCart> cs;
+            for (sdugks_t *h : b->members)
+                if (h->mb.cart && h->precision == mode && narrow(h) == (k == 1)) cs.push_back(h->dc);
+            if (!cs.empty()) plans[mode][k] = plan_cart(cs, mode);
+        }
     std::vector<BatchGroup> want;
     for (size_t k = 0; k < b->members.size(); k++) {
         sdugks_t *h = b->members[k];
         const int D = h->mb.D <= 3 ? 3 : 4, mode = h->precision;
-        const CartPlan &plan = plans[mode];
+        const int nw = h->mb.cart && narrow(h);
+        const CartPlan &plan = plans[mode][nw];
         StepForm form = h->mb.cart ? kMarch : kGeneral;
         if (form == kMarch && plan.threads)
             form = block_wraps(h->dc, cart_block(h->dc, plan.threads, plan.K)) ? kBoxesWrap : kBoxes;
         BatchGroup *g = nullptr;
-        for (auto &x : want) if (x.D == D && x.mode == mode && x.form == form) g = &x;
+        for (auto &x : want) if (x.D == D && x.mode == mode && x.form == form && x.narrow == nw) g = &x;
         if (!g) {
             want.emplace_back();
             g = &want.back();
-            g->D = D; g->mode = mode; g->form = form;
+            g->D = D; g->mode = mode; g->form = form; g->narrow = nw;
             if (form != kGeneral) g->plan = plan;
         }
         g->members.push_back((int)k);
@@ -1060,7 +1066,7 @@ int batch_build_tables(sdugks_batch_t *b)
     bool reuse = want.size() == b->groups.size();
     for (size_t k = 0; reuse && k < want.size(); k++) {
         const BatchGroup &o = b->groups[k], &n = want[k];
-        reuse = o.D == n.D && o.mode == n.mode && o.form == n.form && o.lds >= n.lds && o.cap_inst >= n.n_inst &&
+        reuse = o.D == n.D && o.mode == n.mode && o.form == n.form && o.narrow == n.narrow && o.lds >= n.lds && o.cap_inst >= n.n_inst &&
                 o.cap_tiles >= n.n_tiles &&
                 (n.form == kGeneral ? o.block >= n.block : o.block == n.block && o.plan.K == n.plan.K);
     }

@@ -123,14 +123,14 @@ struct Factors {
 };
 
 // fbar+ of a cell (Eq. fbarplus) from its macros and stored f (in DEV the
-// deviation from w_i rho0 in FP32; in NEQ f - feq); fe: its equilibria as feq9
-// gives them.
+// deviation from w_i rho0 in FP32; in NEQ f - feq).
 template <int PM>
 __device__ __forceinline__ void cell_plus(const DevMesh &m, const Factors<PM> &c, double r, double mu, double mv,
-                                          const Stored<PM> fv[9], Arith<PM> fb[9], double fe[9])
+                                          const Stored<PM> fv[9], Arith<PM> fb[9])
 {
     using R = Arith<PM>;
     const double ir = recip(r);
+    double fe[9];
     feq9(r, mu, mv, mu * ir, mv * ir, PM == SDUGKS_FP32DEV ? m.rho0 : 0.0, fe);
 #pragma unroll
     for (int i = 0; i < 9; i++) fb[i] = fma_(c.ra, (R)fv[i], c.rb[i == 0 ? 0 : (i < 5 ? 1 : 2)] * (R)fe[i]);
@@ -140,13 +140,16 @@ __device__ __forceinline__ void cell_plus(const DevMesh &m, const Factors<PM> &c
 struct WallBC {
     double type, rho, u, v;
 };
-// fbar+ of the boundary state of Section III behind a wall of a cell, from the
-// cell's own (in fb): fbar+_b = fbar+_c + feq(rho_b, u_b) - feq(W_c).
+// The boundary state of Section III behind a wall of a cell differs from the
+// cell's own by fbar+_b - fbar+_c = feq(rho_b, u_b) - feq(W_c), here pair by
+// pair: few cells have walls, and the registers that all 18 equilibria take
+// would be every wave's.
 template <int PM>
-__device__ __forceinline__ void wall_plus(const DevMesh &m, const WallBC &e, double r, double mu, double mv,
-                                          const double fe[9], Arith<PM> fb[9])
+__device__ __forceinline__ void wall_diff(const DevMesh &m, const WallBC &e, double r, double mu, double mv,
+                                          Arith<PM> df[9])
 {
     using R = Arith<PM>;
+    const double off = PM == SDUGKS_FP32DEV ? m.rho0 : 0.0;
     const double ir = recip(r), ux = mu * ir, uy = mv * ir;
     const bool inlet = e.type == SDUGKS_BC_INLET, outlet = e.type == SDUGKS_BC_OUTLET;
     const bool sym = e.type == SDUGKS_BC_SYMMETRY;
@@ -154,10 +157,18 @@ __device__ __forceinline__ void wall_plus(const DevMesh &m, const WallBC &e, dou
     const double rw = inlet ? e.rho : r;                 // inlet / far field
     const double uw = outlet ? ux : (sym ? fma_(-un, e.u, ux) : e.u);
     const double vw = outlet ? uy : (sym ? fma_(-un, e.v, uy) : e.v);
-    double fw[9];
-    feq9(rw, rw * uw, rw * vw, uw, vw, PM == SDUGKS_FP32DEV ? m.rho0 : 0.0, fw);
-#pragma unroll
-    for (int i = 0; i < 9; i++) fb[i] += (R)(cWt[i] * (fw[i] - fe[i]));
+    const double mw = rw * uw, nw = rw * vw;
+    const double Bc = fma_(-1.5, fma_(mu, ux, mv * uy), r - off), Bw = fma_(-1.5, fma_(mw, uw, nw * vw), rw - off);
+    df[0] = (R)(cWt[0] * (Bw - Bc));
+    auto pair = [&](int ip, int iq, double dmc, double duc, double dmw, double duw) {
+        const double Sc = fma_(4.5 * dmc, duc, Bc), Sw = fma_(4.5 * dmw, duw, Bw);
+        df[ip] = (R)(cWt[ip] * (fma_(3.0, dmw, Sw) - fma_(3.0, dmc, Sc)));
+        df[iq] = (R)(cWt[iq] * (fma_(-3.0, dmw, Sw) - fma_(-3.0, dmc, Sc)));
+    };
+    pair(1, 3, mu, ux, mw, uw);
+    pair(2, 4, mv, uy, nw, vw);
+    pair(5, 7, mu + mv, ux + uy, mw + nw, uw + vw);
+    pair(6, 8, mv - mu, uy - ux, nw - mw, vw - uw);
 }
 
 // Least-squares slope along an axis: the normal equations are diagonal on the

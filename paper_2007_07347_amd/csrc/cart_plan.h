@@ -13,25 +13,28 @@
 namespace sdg {
 
 // Times in us that the choice rests on, measured on this chip (256 CUs of four
-// SIMDs): a launch, from the end of the one before it to its first result, and
-// a row of the march or a step of the boxes with one wave and with two waves
-// on every SIMD (the registers allow no third).
+// SIMDs) on cavities of 48 to 1024 cells an edge: a launch, what every round of
+// boxes adds to it (the load of the state), and a row of the march or a step of
+// the boxes with one, two (and, with FP32 arithmetic, three) waves on every
+// SIMD, the most that the registers allow.
 struct CartTimes {
-    double launch, row1, row2, round, step1, step2;
+    double launch, row[2], box_launch, round, step[3];
+    int32_t waves;                      // of boxes on a SIMD
 };
 inline CartTimes cart_times(int precision)
 {
-    if (precision == SDUGKS_FP32DEV) return {2.5, 1.7, 2.35, 1.2, 1.9, 2.5};
-    return {2.5, 1.8, 2.6, 1.2, 2.0, 3.3};
+    if (precision == SDUGKS_FP32DEV) return {2.5, {1.7, 2.35}, 1.8, 1.4, {1.9, 2.5, 3.3}, 3};
+    return {2.5, {1.8, 2.6}, 1.8, 1.6, {2.1, 3.3, 3.3}, 2};
 }
 constexpr int64_t kSimds = 1024;
 constexpr int32_t kWholeSteps = 1000;   // steps per launch of a mesh in one box, at most
 
-// `units` equal waves, two at a time on a SIMD: time per unit of their length.
-inline double cart_rounds(int64_t waves, double one, double two)
+// Time of `waves` equal waves, `most` at a time on a SIMD, which take one + time[k]
+// times `units` with k + 1 of them on it.
+inline double cart_rounds(int64_t waves, int32_t most, double one, const double *time, double units)
 {
-    const int64_t full = waves / (2 * kSimds), rest = waves % (2 * kSimds);
-    return (double)full * two + (rest > kSimds ? two : (rest > 0 ? one : 0.0));
+    const int64_t full = waves / (most * kSimds), rest = (waves % (most * kSimds) + kSimds - 1) / kSimds;
+    return (double)full * (one + units * time[most - 1]) + (rest > 0 ? one + units * time[rest - 1] : 0.0);
 }
 
 struct CartPlan {
@@ -68,7 +71,7 @@ inline CartPlan plan_march(const std::vector<DevCart> &members, int precision)
             waves += (int64_t)c.strips * c.segs;
             longest = std::max(longest, (c.ny + c.segs - 1) / c.segs);
         }
-        const double us = t.launch + (longest + 3.0) * cart_rounds(waves, t.row1, t.row2);
+        const double us = t.launch + cart_rounds(waves, 2, 0.0, t.row, longest + 3.0);
         if (best.rows == 0 || us < best.us) best = {rows, 0, 0, us};
     }
     return best;
@@ -108,7 +111,7 @@ inline CartPlan plan_cart(const std::vector<DevCart> &members, int precision)
 {
     const CartTimes t = cart_times(precision);
     CartPlan best = plan_march(members, precision);
-    for (int32_t threads : {64, 128, 256, 512})
+    for (int32_t threads : {128, 256, 512})
         for (int32_t K : {1, 2, 3, 4, 5, 6, 32}) {      // 32: only where every mesh fits one box
             int64_t boxes = 0;
             bool fits = true;
@@ -118,10 +121,10 @@ inline CartPlan plan_cart(const std::vector<DevCart> &members, int precision)
                 boxes += (int64_t)b.nbx * b.nby;
             }
             if (!fits) continue;
-            // a workgroup of four or eight waves takes one or two on each of a CU's SIMDs
-            const int64_t waves = boxes * (threads / 64);
-            const int64_t slots = threads == 512 ? (boxes + 255) / 256 * 256 * 8 : waves;
-            const double us = (t.launch + cart_rounds(slots, t.round + K * t.step1, t.round + K * t.step2)) / K;
+            // a workgroup of eight waves takes two on each of a CU's SIMDs, and a CU holds one,
+            // with nothing beside it while it loads
+            const double us = (t.box_launch + (threads == 512 ? cart_rounds((boxes + 255) / 256 * 256 * 8, 2, t.round + 0.6, t.step, K)
+                                                              : cart_rounds(boxes * (threads / 64), t.waves, t.round, t.step, K))) / K;
             if (us < best.us) best = {best.rows, threads, K, us};
         }
     return best;

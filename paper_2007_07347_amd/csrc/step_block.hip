@@ -27,6 +27,9 @@ namespace sdg {
 
 namespace {
 
+// Slots of the boundary states below and above the mesh: two rows of at most 64 cells.
+constexpr int kGhosts = 128;
+
 // Boxes along one axis: cells [a, b) are written by box `t`, whose first cell
 // is `o` (outside the mesh: ghost cells or, periodic, wrapped ones).
 struct Span {
@@ -69,19 +72,19 @@ struct Lanes {
 template <typename T>
 __device__ __forceinline__ T ld(const T *base, size_t i) { return gin(base)[i]; }
 
-// `steps` steps of box t of an instance by the whole workgroup (B.threads
-// threads, at least as many as boundary entries); LDS: R [20][threads], the
-// boundary table.
-template <int PM, bool WRAP>
+// `steps` steps of box t of an instance by the whole workgroup (NT = B.threads
+// threads (LDS offsets are then constants), at least as many as boundary entries); LDS: see step_block_lds_bytes.
+template <int PM, bool WRAP, int NT>
 __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg, const DevState &s, const CartBlock &B,
                                             int lagged, int steps, int t)
 {
     using R = Arith<PM>;
     using V = Stored<PM>;
     extern __shared__ double smem[];
-    const int NT = B.threads, bx = 1 << B.log_bx, by = NT >> B.log_bx;
-    R *const sfb = reinterpret_cast<R *>(smem);          // [9][NT] fbar+
-    R *const sup = sfb + 9 * NT;                         // [5][NT] upper sides
+    const int bx = 1 << B.log_bx, by = NT >> B.log_bx;
+    constexpr int NG = NT + kGhosts;
+    R *const sfb = reinterpret_cast<R *>(smem);          // [9][NG] fbar+; below and above the mesh
+    R *const sup = sfb + 9 * NG;                         // [5][NT] upper sides
     R *const sfl = sup + 5 * NT;                         // [6][NT] fluxes through the lower faces
     const int nx = cg.nx, ny = cg.ny;
     const size_t np = (size_t)m.np;
@@ -132,9 +135,9 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
     const gmem<CartRow<R>> *const row = gin((const CartRow<R> *)cg.row) + cj;
     const Factors<PM> c(m);
     const R hl = (R)col[1], hr = (R)col[2], wl = (R)col[3], wr = (R)col[4];
-    const R Cy = (R)col[0] * c.c1, Cy1 = Cy * c.k1, Cy5 = Cy * c.k5;
+    const R Cy = (R)col[0] * c.c1;
     const R hb = row->hb, ht = row->ht, wb = row->wb, wt = row->wt;
-    const R Cx = row->c, Cx1 = Cx * c.k1, Cx5 = Cx * c.k5;
+    const R Cx = row->c;
     const double dtv = (m.dt * col[5]) * row->ih;
     // neighbours: lanes along x, LDS slots along y
     Lanes<WRAP> ln{0, 0};
@@ -145,20 +148,38 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
     }
     const int up = wrap_y && iy + 1 == ny ? ix : (iy + 1 < by ? tid + bx : tid);
     const int dn = iy > 0 ? tid - bx : (wrap_y ? (ny - 1) * bx + ix : tid);
+    const int upb = wall_t ? NT + bx + ix : up, dnb = wall_b ? NT + ix : dn;     // of fbar+
 
     for (int n = 0; n < steps; n++) {
         R fb[9];
-        double fe[9];
-        cell_plus<PM>(m, c, W[0], W[1], W[2], f, fb, fe);
+        cell_plus<PM>(m, c, W[0], W[1], W[2], f, fb);
 #pragma unroll
-        for (int i = 0; i < 9; i++) sfb[i * NT + tid] = fb[i];
+        for (int i = 0; i < 9; i++) sfb[i * NG + tid] = fb[i];
+        // boundary states below and above the mesh, beside the cells
+        if (any_b || any_t) {
+            R df[9];
+            if (wall_b) {
+                wall_diff<PM>(m, bcs[(tags >> 8) & 255], W[0], W[1], W[2], df);
+#pragma unroll
+                for (int i = 0; i < 9; i++) sfb[i * NG + NT + ix] = fb[i] + df[i];
+            }
+            if (wall_t) {
+                wall_diff<PM>(m, bcs[tags >> 16], W[0], W[1], W[2], df);
+#pragma unroll
+                for (int i = 0; i < 9; i++) sfb[i * NG + NT + bx + ix] = fb[i] + df[i];
+            }
+        }
         // slopes along x
         R gx[9], gy[9], dl[3], dr[3];
         {
             R fg[9];
 #pragma unroll
-            for (int i = 0; i < 9; i++) fg[i] = fb[i];
-            if (any_x) wall_plus<PM>(m, bcs[tags & 255], W[0], W[1], W[2], fe, fg);
+            for (int i = 0; i < 9; i++) fg[i] = 0;
+            if (any_x) {
+                wall_diff<PM>(m, bcs[tags & 255], W[0], W[1], W[2], fg);
+#pragma unroll
+                for (int i = 0; i < 9; i++) fg[i] = fb[i] + fg[i];
+            }
 #pragma unroll
             for (int i = 0; i < 9; i++) {
                 const R dn_ = ln.next(fb[i]) - fb[i];
@@ -176,28 +197,9 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         // and along y
         R db[3], dt[3];
         {
-            R gb[9], gt[9];
-#pragma unroll
-            for (int i = 0; i < 9; i++) { gb[i] = sfb[i * NT + dn]; gt[i] = sfb[i * NT + up]; }
-            if (any_b) {
-                R fg[9];
-#pragma unroll
-                for (int i = 0; i < 9; i++) fg[i] = fb[i];
-                wall_plus<PM>(m, bcs[(tags >> 8) & 255], W[0], W[1], W[2], fe, fg);
-#pragma unroll
-                for (int i = 0; i < 9; i++) gb[i] = wall_b ? fg[i] : gb[i];
-            }
-            if (any_t) {
-                R fg[9];
-#pragma unroll
-                for (int i = 0; i < 9; i++) fg[i] = fb[i];
-                wall_plus<PM>(m, bcs[tags >> 16], W[0], W[1], W[2], fe, fg);
-#pragma unroll
-                for (int i = 0; i < 9; i++) gt[i] = wall_t ? fg[i] : gt[i];
-            }
 #pragma unroll
             for (int i = 0; i < 9; i++) {
-                const R dm = fb[i] - gb[i], dp = gt[i] - fb[i];
+                const R dm = fb[i] - sfb[i * NG + dnb], dp = sfb[i * NG + upb] - fb[i];
                 gy[i] = slope(wb, wt, dm, dp);
                 for (int e = 0; e < 3; e++) {
                     if (i == cP[1][e]) db[e] = dm;
@@ -232,7 +234,7 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
                 nb.d = wall_r ? right.d : nb.d;
             }
             R pr[3], nr[3], pl[3], nl[3];
-            face_flux<PM>(m, right, nb, Cx, Cx1, Cx5, pr, nr);
+            face_flux<PM>(m, right, nb, Cx, Cx * c.k1, Cx * c.k5, pr, nr);
 #pragma unroll
             for (int e = 0; e < 3; e++) { pl[e] = ln.prev(pr[e]); nl[e] = ln.prev(nr[e]); }
             outflow_x<0>(acc, pr, nr, pl, nl);
@@ -245,7 +247,7 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         top.s = wall_b ? lower.s : top.s;
         top.d = wall_b ? lower.d : top.d;
         R p[3], q[3];
-        face_flux<PM>(m, top, lower, Cy, Cy1, Cy5, p, q);
+        face_flux<PM>(m, top, lower, Cy, Cy * c.k1, Cy * c.k5, p, q);
 #pragma unroll
         for (int e = 0; e < 3; e++) { sfl[e * NT + tid] = p[e]; sfl[(3 + e) * NT + tid] = q[e]; }
         outflow_below(acc, p, q);
@@ -253,7 +255,7 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         if (any_t) {
             // the face between the last row and the upper wall
             const Side<R> in{{bk[cN[1][0]] + dt[0], bk[cN[1][1]] + dt[1], bk[cN[1][2]] + dt[2]}, upper.s, upper.d};
-            face_flux<PM>(m, upper, in, Cy, Cy1, Cy5, pw, qw);
+            face_flux<PM>(m, upper, in, Cy, Cy * c.k1, Cy * c.k5, pw, qw);
         }
         __syncthreads();
 #pragma unroll
@@ -283,18 +285,18 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         for (int i = 0; i < 3; i++) gout(s.Go)[i * np + g] = G[i];
 }
 
-template <int PM, bool WRAP, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_step_block(DevMesh m, DevCart c, DevState s, CartBlock B, int lagged, int steps)
+template <int PM, bool WRAP, int NT>
+__global__ void __launch_bounds__(NT) k_step_block(DevMesh m, DevCart c, DevState s, CartBlock B, int lagged, int steps)
 {
     const int x = (int)(blockIdx.x % kXcds);
     const int t = xcd_range_start((int)gridDim.x, x) + (int)(blockIdx.x / kXcds);
-    block_steps<PM, WRAP>(m, c, s, B, lagged, steps, t);
+    block_steps<PM, WRAP, NT>(m, c, s, B, lagged, steps, t);
 }
 
 // Batched form: as the batched general step, the slot map gives each workgroup
 // its member and box.
-template <int PM, bool WRAP, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_step_batch_block(BatchTable tab, int steps, int parity)
+template <int PM, bool WRAP, int NT>
+__global__ void __launch_bounds__(NT) k_step_batch_block(BatchTable tab, int steps, int parity)
 {
     const int x = (int)(blockIdx.x % kXcds);
     const int per = (int)gridDim.x / kXcds;
@@ -305,14 +307,16 @@ __global__ void __launch_bounds__(MAXT) k_step_batch_block(BatchTable tab, int s
     const DevMesh m = in.m;
     const DevCart cg = in.c;
     const CartBlock B = in.b;
-    block_steps<PM, WRAP>(m, cg, batch_state(in, parity), B, in.lagged, steps, box);
+    block_steps<PM, WRAP, NT>(m, cg, batch_state(in, parity), B, in.lagged, steps, box);
 }
 
 }  // namespace
 
 size_t step_block_lds_bytes(int threads, int mode, int n_bc)
 {
-    return (size_t)20 * threads * (mode == SDUGKS_FP32DEV ? sizeof(float) : sizeof(double)) + n_bc * sizeof(WallBC);
+        // fbar+ of the cells and the boundary states, upper sides, fluxes
+    return (20 * (size_t)threads + 9 * kGhosts) * (mode == SDUGKS_FP32DEV ? sizeof(float) : sizeof(double)) +
+           n_bc * sizeof(WallBC);
 }
 
 hipError_t launch_step_block(const DevMesh &m, const DevCart &c, const DevState &s, const CartBlock &B, int lagged,
@@ -321,28 +325,30 @@ hipError_t launch_step_block(const DevMesh &m, const DevCart &c, const DevState 
     const dim3 grid((unsigned)(B.nbx * B.nby)), blk((unsigned)B.threads);
     const size_t lds = step_block_lds_bytes(B.threads, mode, m.n_bc);
     const bool wrap = block_wraps(c, B);
+#define SDG_NT(PP, WW, NN) emit(&k_step_block<PP, WW, NN>, grid, blk, lds, st, gc, m, c, s, B, lagged, steps)
 #define SDG_BLOCK(PP, WW) \
-    return B.threads <= 256 ? emit(&k_step_block<PP, WW, 256>, grid, blk, lds, st, gc, m, c, s, B, lagged, steps) \
-                            : emit(&k_step_block<PP, WW, 512>, grid, blk, lds, st, gc, m, c, s, B, lagged, steps)
+    return B.threads == 128 ? SDG_NT(PP, WW, 128) : (B.threads == 256 ? SDG_NT(PP, WW, 256) : SDG_NT(PP, WW, 512))
     if (mode == SDUGKS_FP32DEV) { if (wrap) SDG_BLOCK(SDUGKS_FP32DEV, true); SDG_BLOCK(SDUGKS_FP32DEV, false); }
     if (mode == SDUGKS_FP32NEQ) { if (wrap) SDG_BLOCK(SDUGKS_FP32NEQ, true); SDG_BLOCK(SDUGKS_FP32NEQ, false); }
     if (wrap) SDG_BLOCK(SDUGKS_FP64, true);
     SDG_BLOCK(SDUGKS_FP64, false);
 #undef SDG_BLOCK
+#undef SDG_NT
 }
 
 hipError_t launch_step_batch_block(const BatchTable &tab, bool wrap, int threads, int mode, int steps, int parity,
                                    int cap_tiles, size_t lds, hipStream_t st, GraphChain *gc)
 {
     const dim3 grid((unsigned)batch_grid(cap_tiles)), blk((unsigned)threads);
+#define SDG_NT(PP, WW, NN) emit(&k_step_batch_block<PP, WW, NN>, grid, blk, lds, st, gc, tab, steps, parity)
 #define SDG_BLOCK(PP, WW) \
-    return threads <= 256 ? emit(&k_step_batch_block<PP, WW, 256>, grid, blk, lds, st, gc, tab, steps, parity) \
-                          : emit(&k_step_batch_block<PP, WW, 512>, grid, blk, lds, st, gc, tab, steps, parity)
+    return threads == 128 ? SDG_NT(PP, WW, 128) : (threads == 256 ? SDG_NT(PP, WW, 256) : SDG_NT(PP, WW, 512))
     if (mode == SDUGKS_FP32DEV) { if (wrap) SDG_BLOCK(SDUGKS_FP32DEV, true); SDG_BLOCK(SDUGKS_FP32DEV, false); }
     if (mode == SDUGKS_FP32NEQ) { if (wrap) SDG_BLOCK(SDUGKS_FP32NEQ, true); SDG_BLOCK(SDUGKS_FP32NEQ, false); }
     if (wrap) SDG_BLOCK(SDUGKS_FP64, true);
     SDG_BLOCK(SDUGKS_FP64, false);
 #undef SDG_BLOCK
+#undef SDG_NT
 }
 
 }  // namespace sdg

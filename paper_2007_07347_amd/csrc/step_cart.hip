@@ -206,16 +206,13 @@ struct March {
         const bool beyond = k == klow || k == khigh;
         int tag = side;
         if (beyond) tag = gin(cg.side)[(k == klow ? 0 : cg.nx) + cc];
-        double fe[9];
-        cell_plus<PM>(m, c, W[0], W[1], W[2], fv, fb, fe);
+        cell_plus<PM>(m, c, W[0], W[1], W[2], fv, fb);
         if (edge || beyond) {
             // columns and rows outside a wall read the cell inside it and hold the boundary state
-            R fw[9];
+            R df[9];
+            wall_diff<PM>(m, bcs[tag < 0 ? 0 : tag], W[0], W[1], W[2], df);
 #pragma unroll
-            for (int i = 0; i < 9; i++) fw[i] = fb[i];
-            wall_plus<PM>(m, bcs[tag < 0 ? 0 : tag], W[0], W[1], W[2], fe, fw);
-#pragma unroll
-            for (int i = 0; i < 9; i++) fb[i] = tag < 0 ? fb[i] : fw[i];
+            for (int i = 0; i < 9; i++) fb[i] = tag < 0 ? fb[i] : fb[i] + df[i];
         }
     }
     // W and f of the row in ring slot t, put there when it arrived
