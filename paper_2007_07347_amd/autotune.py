@@ -1,10 +1,9 @@
 """Autotuner of the fused step's schedule: on tensor-product quad meshes the
-structured step (fixed tiles, one lane per face) against the
-general fused step; for the general step, the tile size (cells per
-workgroup, which sets the halo overhead and the LDS per workgroup, hence how
-many workgroups share a compute unit) and threads per workgroup (which sets
-how many lanes serve each cell in every phase: four per cell, one per face
-of a quad, in the face pass).
+structured step (which cuts a mesh by its size) against the general fused
+step; for the general step, the tile size (cells per workgroup, which sets the
+halo overhead and the LDS per workgroup, hence how many workgroups share a
+compute unit) and threads per workgroup (0: the library's choice, with which a
+thread may take a second cell and face).
 
 Each candidate is built with the library, warmed up, and timed with HIP
 events over a fixed number of steps on the instance's own stream; the
@@ -22,18 +21,17 @@ import numpy as np
 from . import sdugks
 
 # (tile cells, threads) of the general step: a tile holds at most a quarter as
-# many cells as threads
-CANDIDATES = [(16, 64), (16, 128), (32, 128), (16, 256), (32, 256), (64, 256)]
+# many cells as threads, unless the threads are left to the library (0)
+CANDIDATES = [(16, 64), (16, 128), (32, 128), (16, 256), (32, 256), (64, 256), (64, 0)]
 STRUCTURED = {"structured": 2}
 
 
 def label(sched):
-    """Name of a schedule in timing tables: the lanes-per-face axis (one lane
-    per face on the structured step, four lanes per cell, one per face slot,
-    on the general step) and the general step's tile cells / threads."""
+    """Name of a schedule in timing tables: the structured step, or the general
+    step's tile cells / threads."""
     if sched.get("structured") == 2:
-        return "structured, 1 lane per face"
-    return f"general {sched['tile_cells']}/{sched['block_threads']}, 4 lanes per cell"
+        return "structured"
+    return f"general {sched['tile_cells']}/{sched['block_threads'] or 'auto'}"
 
 
 def candidates_for(problems, candidates=None):

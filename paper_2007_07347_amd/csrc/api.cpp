@@ -50,7 +50,7 @@ struct Layout {
     size_t off_f[2]{}, off_W[2]{}, off_G[2]{}, off_fbp = 0, off_sg = 0, off_snap = 0;
     size_t off_nbr = 0, off_geo = 0, off_ainv = 0, off_dtv = 0, off_area = 0, off_bft = 0, off_bcs = 0;
     size_t off_part = 0, off_out = 0, total = 0;
-    size_t off_thdr = 0, off_lgid = 0, off_ladj = 0, off_lfc = 0, off_frec = 0, off_lw = 0;
+    size_t off_thdr = 0, off_lgid = 0, off_ladj = 0, off_lfc = 0, off_fcell = 0, off_frec = 0, off_lw = 0;
     size_t off_bq_hdr = 0, off_bq_nb = 0, off_bq_w = 0, off_bq_geo = 0, off_bq_out = 0, off_bq_sum = 0;
     size_t off_ccol = 0, off_crow = 0, off_cside = 0;
 };
@@ -85,6 +85,7 @@ Layout make_layout(const MeshBuild &mb, int precision)
         L.off_lgid = take(mb.lgid.size() * sizeof(int32_t));
         L.off_ladj = take(mb.ladj.size() * sizeof(int16_t));
         L.off_lfc = take(mb.lfc.size() * sizeof(int16_t));
+        L.off_fcell = take(mb.fcell.size() * sizeof(int32_t));
         L.off_frec = take(mb.frec.size() * (dev ? sizeof(float) : sizeof(double)));
         L.off_lw = take(mb.lw.size() * (dev ? sizeof(float) : sizeof(double)));
     } else {
@@ -127,7 +128,8 @@ struct sdugks_s {
     bool diverged = false;
     int precision = SDUGKS_FP64, macro = SDUGKS_MACRO_CURRENT, scheme = SDUGKS_SCHEME_SIMPLIFIED;
     double rho0 = 1.0;
-    int block = 256;
+    int block = 0;               // threads of the general step
+    bool own_block = false;      // ... the library's choice
     DevMesh dm{};
     DevTiles dt{};
     DevCart dc{};
@@ -166,6 +168,7 @@ struct BatchGroup {
     int D = 4, mode = 0, block = 64;
     StepForm form = kGeneral;
     int narrow = 0;
+    bool own_block = true, two = false;     // general step: the library's choice of threads; second cells or faces
     CartPlan plan;
     size_t lds = 0;
     int n_inst = 0, n_tiles = 0, cap_inst = 0, cap_tiles = 0;
@@ -410,7 +413,8 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         return fail(SDUGKS_ENODEV, "the current device is not gfx950");
     }
     h->stream = (hipStream_t)stream;
-    h->block = prm->block_threads ? prm->block_threads : 256;
+    h->block = prm->block_threads;
+    h->own_block = h->block == 0;
     h->precision = prm->precision;
     h->macro = prm->macro_flux;
     h->scheme = prm->scheme;
@@ -557,6 +561,7 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
             !up(L.off_lgid, mb.lgid.data(), mb.lgid.size() * sizeof(int32_t)) ||
             !up(L.off_ladj, mb.ladj.data(), mb.ladj.size() * sizeof(int16_t)) ||
             !up(L.off_lfc, mb.lfc.data(), mb.lfc.size() * sizeof(int16_t)) ||
+            !up(L.off_fcell, mb.fcell.data(), mb.fcell.size() * sizeof(int32_t)) ||
             !(dev ? up(L.off_frec, frec32.data(), frec32.size() * sizeof(float))
                   : up(L.off_frec, mb.frec.data(), mb.frec.size() * sizeof(double))) ||
             !(dev ? up(L.off_lw, lw32.data(), lw32.size() * sizeof(float))
@@ -567,10 +572,12 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         h->dt.na_max = mb.na_max;
         h->dt.nt_max = mb.nt_max;
         h->dt.nf_max = std::max<int32_t>(1, mb.nf_max);
+        if (h->own_block) h->block = step_tiled_block(h->dt, mb.n_tiles);
         h->dt.hdr = h->at<int32_t>(L.off_thdr);
         h->dt.lgid = h->at<int32_t>(L.off_lgid);
         h->dt.ladj = h->at<int16_t>(L.off_ladj);
         h->dt.lfc = h->at<int16_t>(L.off_lfc);
+        h->dt.fcell = h->at<int32_t>(L.off_fcell);
         h->dt.fr = dev ? nullptr : h->at<double2>(L.off_frec);
         h->dt.fr32 = dev ? h->at<float2>(L.off_frec) : nullptr;
         h->dt.lw = dev ? nullptr : h->at<double2>(L.off_lw);
@@ -1054,6 +1061,7 @@ int batch_build_tables(sdugks_batch_t *b)
         size_t lds = march_lds_bytes(n_bc);
         if (form == kGeneral) {
             g->block = std::max(g->block, h->block);
+            g->own_block = g->own_block && h->own_block;
             lds = step_tiled_lds_bytes(h->dt, mode, n_bc);
         } else if (form != kMarch) {
             g->block = plan.threads;
@@ -1063,12 +1071,20 @@ int batch_build_tables(sdugks_batch_t *b)
         g->n_inst++;
         g->n_tiles += member_tiles(h, *g);
     }
+    for (auto &g : want) {
+        if (g.form != kGeneral) continue;
+        if (g.own_block) {
+            g.block = 256;
+            for (int k : g.members) g.block = std::min(g.block, step_tiled_block(b->members[k]->dt, g.n_tiles));
+        }
+        for (int k : g.members) g.two = g.two || step_tiled_two(b->members[k]->dt, g.block);
+    }
     bool reuse = want.size() == b->groups.size();
     for (size_t k = 0; reuse && k < want.size(); k++) {
         const BatchGroup &o = b->groups[k], &n = want[k];
         reuse = o.D == n.D && o.mode == n.mode && o.form == n.form && o.narrow == n.narrow && o.lds >= n.lds && o.cap_inst >= n.n_inst &&
                 o.cap_tiles >= n.n_tiles &&
-                (n.form == kGeneral ? o.block >= n.block : o.block == n.block && o.plan.K == n.plan.K);
+                o.block == n.block && o.two == n.two && o.plan.K == n.plan.K;
     }
     if (!reuse) {
         batch_release_graph(b);
@@ -1164,7 +1180,7 @@ hipError_t batch_launch(sdugks_batch_t *b, const BatchGroup &g, int steps, int p
 {
     const BatchTable tab{g.d_inst, g.d_tmap};
     if (g.form == kGeneral)
-        return launch_step_batch(tab, g.D, g.mode, parity, g.cap_tiles, g.lds, g.block, b->stream, gc);
+        return launch_step_batch(tab, g.D, g.mode, g.two, parity, g.cap_tiles, g.lds, g.block, b->stream, gc);
     if (g.form == kMarch) return launch_step_batch_cart(tab, g.mode, parity, g.cap_tiles, g.lds, b->stream, gc);
     return launch_step_batch_block(tab, g.form == kBoxesWrap, g.block, g.mode, steps, parity, g.cap_tiles, g.lds,
                                    b->stream, gc);

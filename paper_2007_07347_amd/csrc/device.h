@@ -50,7 +50,8 @@ struct DevState {
 };
 
 // Tiles of the fused step (see MeshBuild): headers [n_tiles][8] (g0, nt, n1,
-// n2), the padded per-tile tables lgid [PL], ladj [D][PA], lfc [D][PT] and the
+// n2, faces), the padded per-tile tables lgid [PL], ladj [D][PA], lfc [D][PT], the
+// cells of every face fcell [PF], the
 // face records [3][PF] (rows l n, r_self, r_other of (x, y) pairs) and the
 // least-squares weights lw [D][PA] ((x, y) pairs), with PL = nl_max,
 // PA = na_max, PT = nt_max, PF = nf_max.
@@ -60,6 +61,7 @@ struct DevTiles {
     const int32_t *lgid;
     const int16_t *ladj;
     const int16_t *lfc;
+    const int32_t *fcell;
     const double2 *fr, *lw;             // FP64 form
     const float2 *fr32, *lw32;          // deviation form
 };
@@ -185,6 +187,17 @@ hipError_t launch_flux_update(const DevMesh &m, const DevState &s, const DevScra
 hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState &s, int lagged, int mode,
                              int block, hipStream_t st, GraphChain *gc = nullptr);
 size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc);
+// More local cells or faces than threads (never more than twice as many, nor
+// more cells of tile and first ring than threads).
+inline bool step_tiled_two(const DevTiles &t, int block) { return t.nl_max > block || t.nf_max > block; }
+// Threads of the fused step where the caller leaves them to the library: four
+// waves a tile while all tiles are on the chip at once (three per CU in FP64:
+// a 45,000-cell mesh takes 8.0 us a step, with two waves 8.3), two beyond (a
+// 200,000-cell mesh with FP32 deviations takes 14.3 us, with four waves 17.1).
+inline int step_tiled_block(const DevTiles &t, int64_t n_tiles)
+{
+    return n_tiles <= 768 && !step_tiled_two(t, 256) ? 256 : 128;
+}
 // Structured step over the tiles of a tensor-product quad mesh (one
 // workgroup per tile: 16 x 14 cells on 512 threads for FP32 deviations, 16 x 7
 // on 256 threads otherwise), and its batched form (members of one mode on the
@@ -209,7 +222,7 @@ inline int32_t cart_groups(const DevCart &c) { return c.strips * c.segs; }
 hipError_t launch_step_batch_cart(const BatchTable &tab, int mode, int parity, int cap_tiles, size_t lds,
                                   hipStream_t st, GraphChain *gc = nullptr);
 // Batched fused step over the tiles of all members (same D class and mode).
-hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, int parity, int cap_tiles, size_t lds,
+hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds,
                              int block, hipStream_t st, GraphChain *gc = nullptr);
 // Deterministic reductions of the residual / mass / finiteness check: writes
 // out4 = {sum |u-u_snap|^2, sum |u_snap|^2, sum V rho, count of non-finite}.

@@ -205,6 +205,7 @@ bool build_tiles(MeshBuild &out, std::vector<std::pair<size_t, size_t>> parts)
     std::vector<int32_t> rec_of(n_face_ids, -1);
     std::vector<std::vector<double>> recs(out.n_tiles);
     std::vector<std::vector<int16_t>> codes(out.n_tiles);
+    std::vector<std::vector<int32_t>> ends(out.n_tiles);
     out.nt_max = out.nf_max = 0;
     for (int32_t t = 0; t < out.n_tiles; t++) out.nt_max = std::max(out.nt_max, out.tile_hdr[(size_t)t * 8 + 1]);
     const size_t PT = out.nt_max;
@@ -224,6 +225,7 @@ bool build_tiles(MeshBuild &out, std::vector<std::pair<size_t, size_t>> parts)
                     rec_of[f] = (int32_t)(R.size() / 6);
                     used.push_back(f);
                     R.insert(R.end(), v, v + 6);
+                    ends[t].push_back(k | (int32_t)((uint32_t)out.ladj[((size_t)t * D + s) * PA + k] << 16));
                     code = 2 * rec_of[f];
                 } else {
                     const double *r = &R[(size_t)rec_of[f] * 6];
@@ -234,13 +236,16 @@ bool build_tiles(MeshBuild &out, std::vector<std::pair<size_t, size_t>> parts)
                 codes[t][(size_t)s * PT + k] = (int16_t)code;
             }
         for (int32_t f : used) rec_of[f] = -1;
+        out.tile_hdr[(size_t)t * 8 + 4] = (int32_t)(R.size() / 6);
         out.nf_max = std::max(out.nf_max, (int32_t)(R.size() / 6));
     }
     const size_t PF = std::max<int32_t>(1, out.nf_max);
     out.lfc.assign((size_t)out.n_tiles * D * PT, -1);
     out.frec.assign((size_t)out.n_tiles * 3 * PF * 2, 0.0);
+    out.fcell.assign((size_t)out.n_tiles * PF, 0);
     for (int32_t t = 0; t < out.n_tiles; t++) {
         std::copy(codes[t].begin(), codes[t].end(), out.lfc.begin() + (size_t)t * D * PT);
+        std::copy(ends[t].begin(), ends[t].end(), out.fcell.begin() + (size_t)t * PF);
         const std::vector<double> &R = recs[t];
         for (size_t r = 0; r < R.size() / 6; r++)
             for (size_t k = 0; k < 3; k++)
@@ -524,7 +529,8 @@ int build_mesh(const sdugks_mesh *m, const sdugks_bc *bc, int32_t n_bc, const sd
     std::vector<int32_t> perm(nc), iperm(nc);
     const bool tiled = prm->tile_cells >= 0 && D <= 4 && n_bc <= kMaxTileBcs;
     const int32_t B = prm->block_threads > 0 ? prm->block_threads : kDefaultBlock;
-    int32_t T = prm->tile_cells > 0 ? std::min(prm->tile_cells, B / 4) : B / 4;
+    const int32_t most = prm->block_threads > 0 ? B / 4 : kDefaultTile;
+    int32_t T = prm->tile_cells > 0 ? std::min(prm->tile_cells, most) : most;
     if (tiled && T < 4) BAD("tile_cells must be at least 4 (or 0 / -1)");
     std::vector<std::pair<size_t, size_t>> parts;
     if (cart) {
@@ -637,7 +643,7 @@ int build_mesh(const sdugks_mesh *m, const sdugks_bc *bc, int32_t n_bc, const sd
         if (bc[t].type == SDUGKS_BC_SYMMETRY) { out.bcs[t].u = sym_nx[t]; out.bcs[t].v = sym_ny[t]; }   // the line's normal
     }
     out.tile_T = 0; out.n_tiles = 0;
-    out.tile_hdr.clear(); out.lgid.clear(); out.ladj.clear(); out.lfc.clear(); out.frec.clear(); out.lw.clear();
+    out.tile_hdr.clear(); out.lgid.clear(); out.ladj.clear(); out.lfc.clear(); out.fcell.clear(); out.frec.clear(); out.lw.clear();
     out.cart = cart;
     if (cart) {
         // per column / row: width, face offsets, least-squares weights of the
@@ -669,8 +675,10 @@ int build_mesh(const sdugks_mesh *m, const sdugks_bc *bc, int32_t n_bc, const sd
         out.tile_T = kCartTX * rows;
     } else if (tiled) {
         if (!build_tiles(out, parts)) BAD("internal: the two views of a face are not exact mirrors");
-        if (tile_lds_bytes(out.nl_max, out.na_max, out.nt_max, n_bc) > kTileLdsLimit || out.nl_max > B) {
-            // one thread per local cell and LDS for all of them: bisect into smaller tiles
+        if (tile_lds_bytes(out.nl_max, out.na_max, out.nt_max, out.nf_max, n_bc) > kTileLdsLimit ||
+            (prm->block_threads > 0 ? std::max(out.nl_max, out.nf_max) > B
+                                    : out.na_max > B || std::max(out.nl_max, out.nf_max) > 2 * B)) {
+            // threads for all local cells and faces, and LDS for all of them: bisect into smaller tiles
             if (T <= 4) BAD("mesh too irregular for the fused step's tiles");
             sdugks_params smaller = *prm;
             smaller.tile_cells = T / 2;

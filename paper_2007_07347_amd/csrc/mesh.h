@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -62,13 +63,17 @@ struct MeshBuild {
     //                               between two tile cells is stored once; the
     //                               other cell's view is (-l n, r_other, r_self),
     //                               the exact mirror the per-slot arrays hold.
+    //   fcell [n_tiles][PF]         its two cells: local index of the first, and in
+    //                               the upper 16 bits the local index of the
+    //                               second or -2 - tag (as ladj);
     //   lw   [n_tiles][D][PA][2]    least-squares weight (x, y) behind each slot
     //                               of a tile or first-ring cell.
     int32_t tile_T = 0, n_tiles = 0, nl_max = 0, na_max = 0, nt_max = 0, nf_max = 0;
-    std::vector<int32_t> tile_hdr;   // [n_tiles][8]: g0, nt, n1, n2, 0...
+    std::vector<int32_t> tile_hdr;   // [n_tiles][8]: g0, nt, n1, n2, faces, 0...
     std::vector<int32_t> lgid;
     std::vector<int16_t> ladj;
     std::vector<int16_t> lfc;
+    std::vector<int32_t> fcell;
     std::vector<double> frec;
     std::vector<double> lw;
     // Structured step (tensor-product quad meshes; cart == true): the cells
@@ -115,23 +120,20 @@ __host__ __device__ inline int32_t xcd_range_start(int32_t n, int32_t x)
 }
 // Boundary-condition entries the fused step keeps in LDS (more: two-kernel step).
 constexpr int32_t kMaxTileBcs = 64;
-// LDS words per cell of the fused step's gradient array: the 18 components
-// and one pad, so that consecutive cells fall on different LDS banks (an odd
-// number of words in FP32, an odd number of word pairs in FP64).
-constexpr int32_t kGradStride = 19;
-// LDS bytes of one workgroup of the fused step: rho and u of every tile or
-// first-ring cell and the momentum of every tile cell (FP64), fbar+ of every
-// local cell and the gradient of every tile or first-ring cell (elem bytes:
-// 8 FP64, 4 deviation form), then the boundary-condition table (4 doubles
-// per entry).
-inline size_t tile_lds_bytes(int32_t nl_max, int32_t na_max, int32_t nt_max, int32_t n_bc, size_t elem = 8)
+// LDS bytes of one workgroup of the fused step (elem: bytes of its arithmetic):
+// W of the tile cells in FP64, the boundary table, slopes and carried-back
+// fbar+ of every tile or first-ring cell, fbar+ of every local cell or the
+// fluxes of the faces.
+inline size_t tile_lds_bytes(int32_t nl_max, int32_t na_max, int32_t nt_max, int32_t nf_max, int32_t n_bc, size_t elem = 8)
 {
-    const size_t head = (3 * (size_t)na_max + 2 * (size_t)nt_max) * 8 +
-                        (9 * (size_t)nl_max + kGradStride * (size_t)na_max) * elem;
-    return (head + 15) / 16 * 16 + 32 * (size_t)n_bc;
+    const size_t last = std::max(9 * (size_t)nl_max, 8 * (size_t)nf_max);
+    return (3 * (size_t)nt_max + 1) / 2 * 16 + 32 * (size_t)n_bc + (27 * (size_t)na_max + last) * elem;
 }
 constexpr size_t kTileLdsLimit = 64 * 1024;
-constexpr int32_t kDefaultBlock = 256;   // threads of the fused step; tiles hold at most a quarter as many cells
+// Threads of the fused step by default, on tiles of 64 cells; with a number of
+// threads given, tiles hold at most a quarter as many cells and every local cell
+// and face has a thread of its own.
+constexpr int32_t kDefaultBlock = 128, kDefaultTile = 64;
 
 // Returns SDUGKS_OK or an error code with a message in err.
 int build_mesh(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, const sdugks_params *prm,

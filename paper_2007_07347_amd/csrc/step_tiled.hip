@@ -1,47 +1,52 @@
 // Fused sDUGKS time step (Zhong et al., arXiv:2007.07347, Section II, the
-// eleven-step summary) in one kernel: one workgroup per tile of cells, at
-// most one work item per thread in every phase.
+// eleven-step summary) in one kernel for any mesh of triangles and quads: one
+// workgroup per tile of cells.  A thread takes one cell of the tile or its first
+// halo ring and, where there are more of them than threads, another of the
+// second ring and a second face: two waves for a tile of 64 cells keep their
+// lanes busier than four, and twice as many tiles fit a CU.
 //
 //   phase 1  fbar+ = a f + b feq(W) (Eq. fbarplus) of the tile and its two
-//            halo rings into LDS, with the macros later phases read (rho and
-//            u of the tile and first ring, the momentum of the tile); halo
-//            values are recomputed by every tile that needs them instead of
-//            being stored to memory;
-//   phase 2  least-squares gradient of fbar+ (the LLSR normal equations solved
+//            halo rings into LDS; halo values are recomputed by every tile that
+//            needs them instead of being stored to memory;
+//   phase 2  least-squares slopes of fbar+ (the LLSR normal equations solved
 //            through precomputed weights A^-1 d; boundary states are points at
-//            the face midpoints) for the tile and its first ring, into LDS (in
-//            FP64 the two halves of the workgroup take velocities 0..4 and
-//            5..8 of the same cells when those fit in one half);
-//   phase 3  four lanes per tile cell, one face each: upwind reconstruction at
-//            the foot point (Eq. fbpsource), face macros and equilibrium,
-//            f at the face (Eq. f_t_n+1), mesoscopic and macroscopic fluxes
-//            (Eqs. MesoFlux, MacroFlux); per-cell sums by lane shuffles in a
-//            fixed order; then W^{n+1} (Eq. MacroUpdate), feq^{n+1} and
-//            f^{n+1} (Eq. fn+1), each lane writing two or three velocities.
+//            the face midpoints) for the tile and its first ring, into LDS with
+//            fbar+ carried back along every velocity, b_i = fbar+_i - dt e_i.g_i;
+//   phase 3  one lane per face of the tile's cells: the upwind value of every
+//            velocity at the foot point (Eq. fbpsource), b_i + r.g_i with r from
+//            the upwind cell's centre to the face; face macros and equilibrium,
+//            f at the face (Eq. f_t_n+1) and its mesoscopic fluxes (Eq. MesoFlux)
+//            into LDS, over fbar+;
+//   phase 4  one lane per tile cell: the fluxes of its faces summed in FP64 in the
+//            order of its slots, W^{n+1} (Eq. MacroUpdate), feq^{n+1}, f^{n+1}
+//            (Eq. fn+1), from the state the lane read in phase 1.
+//
+// Velocities are taken by opposite pairs: of each pair one leaves a face's
+// first cell and the other its second, so a pair needs one reconstruction from
+// each cell, at indices that the sign of e.n selects.
 //
 // Three forms share the code (template parameter PM), all with FP64 density
-// and momentum, their update and the macroscopic fluxes:
+// and momentum, their update and the flux sums:
 //   PM = 0  f stored and computed in FP64;
 //   PM = 1  the deviation f - w_i rho0 stored in FP32 with FP32 face records
-//           and least-squares weights, fbar+, gradients and face fluxes
-//           computed in FP32 on deviations (the constant parts cancel
-//           exactly: sum_i w_i e_i = 0 and the scaled normals of a closed cell
-//           sum to zero), per-cell flux sums compensated (TwoSum);
+//           and least-squares weights, fbar+, slopes and face fluxes computed in
+//           FP32 on deviations (the constant parts cancel exactly: sum_i w_i e_i
+//           = 0 and the scaled normals of a closed cell sum to zero);
 //   PM = 2  the non-equilibrium part f - feq(W) stored in FP32 (FP32 tables),
 //           every operation in FP64: f = feq(W) + stored part on load, and
 //           f^{n+1} - feq(W^{n+1}) rounded to FP32 on store.
 //
-// Every global input of phases 2 and 3 (adjacency, least-squares weights,
-// face records) is requested at kernel start, so its latency overlaps phase 1.
-// The faces of a tile's cells are one table of records per tile: a face
-// between two tile cells is read once and used by both cells, mirrored.  Each
-// XCD sweeps a contiguous range of bisection tiles, those with boundary faces
-// first, so the halo cells a tile reads are mostly L2 hits and the slower
-// tiles start earliest.  A face shared by two tiles is evaluated by both from
-// identical operands: the flux that leaves one cell enters the other exactly.
+// Every global input of the later phases is requested at kernel start, so its
+// latency overlaps phase 1.  Each XCD sweeps a contiguous range of bisection
+// tiles, those with boundary faces first, so the halo cells a tile reads are
+// mostly L2 hits and the slower tiles start earliest.  A face shared by two
+// tiles is evaluated by both, perhaps from opposite sides: exchanging the cells
+// and the sign of n exchanges the operands of commutative operations only, so
+// the flux that leaves one cell enters the other exactly.
 #include <type_traits>
 #include <utility>
 
+#include "cart_math.h"
 #include "d2q9.h"
 #include "device.h"
 #include "mesh.h"
@@ -51,338 +56,270 @@ namespace sdg {
 
 namespace {
 
-// Least-squares gradient of fbar+ for velocities [I0, I1) of local cell c:
-// sum over its stencil of w (value - fbar+_c), boundary points carrying
-// fbar+_b - fbar+_c = feq(rho_b, u_b) - feq(W_c).
-template <int I0, int I1, int D, typename R>
-__device__ __forceinline__ void gradient_cell(const R *sfbp, R *ssg, const double *sW, const double *sbc, int P1, int c,
-                                              const int *la2, const R *wx2, const R *wy2)
-{
-    constexpr int N = I1 - I0, SG = kGradStride;
-    R ax[N], ay[N], fc[N];
-    static_for<N>([&](auto K) {
-        ax[K] = 0;
-        ay[K] = 0;
-        fc[K] = sfbp[c * 9 + I0 + K];
-    });
-#pragma unroll
-    for (int sl = 0; sl < D; sl++) {
-        const int la = la2[sl];
-        if (la == -1) continue;
-        if (la >= 0) {
-            static_for<N>([&](auto K) {
-                const R df = sfbp[la * 9 + I0 + K] - fc[K];
-                ax[K] += wx2[sl] * df;
-                ay[K] += wy2[sl] * df;
-            });
-        } else {
-            const double r = sW[c], ux = sW[P1 + c], uy = sW[2 * P1 + c];
-            double rb, ub, vb;
-            boundary_state_t(sbc, -2 - la, r, ux, uy, rb, ub, vb);
-            const double uu = ux * ux + uy * uy, uub = ub * ub + vb * vb;
-            static_for<N>([&](auto K) {
-                constexpr int i = I0 + K;
-                const R df = (R)(feq_c<cEx[i], cEy[i]>(cW[i], rb, ub, vb, uub) -
-                                 feq_c<cEx[i], cEy[i]>(cW[i], r, ux, uy, uu));
-                ax[K] += wx2[sl] * df;
-                ay[K] += wy2[sl] * df;
-            });
-        }
-    }
-    static_for<N>([&](auto K) {
-        ssg[c * SG + I0 + K] = ax[K];
-        ssg[c * SG + 9 + I0 + K] = ay[K];
-    });
-}
+// Opposite velocities: pair k is cPair[k][0] and cPair[k][1].
+constexpr int cPair[4][2] = {{1, 3}, {2, 4}, {5, 7}, {6, 8}};
 
-// One time step of tile t of one instance (the whole workgroup takes part).
-template <int D, int PM>
+// One time step of tile t of one instance (the whole workgroup takes part).  TWO:
+// more local cells or faces than threads, so threads take second ones.
+template <int D, int PM, bool TWO>
 __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, const DevState &s, int lagged, int t)
 {
-    constexpr bool S32 = PM != 0;    // f and the tables stored in FP32
-    constexpr bool DEV = PM == 1;    // FP32 arithmetic on deviations from the rest state w_i rho0
-    constexpr bool NEQ = PM == 2;    // stored: f - feq(W); arithmetic in FP64
-    using R = typename std::conditional<DEV, float, double>::type;   // arithmetic of fbar+, gradients, faces
+    using R = Arith<PM>;                        // arithmetic of fbar+, slopes, faces
+    using V = Stored<PM>;
+    using T = typename std::conditional<PM == SDUGKS_FP64, double, float>::type;    // tables
+    using T2 = typename std::conditional<PM == SDUGKS_FP64, double2, float2>::type;
+    struct R3 {
+        R b, x, y;
+    };
     extern __shared__ double smem[];
-    const int P = tl.nl_max, P1 = tl.na_max, PT = tl.nt_max;
-    const int np = m.np;
+    const int P = tl.nl_max, PA = tl.na_max, PT = tl.nt_max, PF = tl.nf_max;
+    const size_t np = (size_t)m.np;
     const int tid = threadIdx.x;
-    // macros: rho, u, v of the tile and first-ring cells [3][P1] (the
-    // boundary states need them), rho u, rho v of the tile cells [2][PT] (the
-    // update needs them); nothing for the second ring
-    double *sW = smem;
-    double *sM = smem + 3 * P1;
-    // per cell: fbar+ [P][9] (deviation in DEV) and its gradient [P1][SG]
-    // (x components 0..8, y components 9..17, one pad); cell-major, so the
-    // velocity and component are constant offsets of one per-cell address
-    R *sfbp = reinterpret_cast<R *>(smem + 3 * P1 + 2 * PT);
-    R *ssg = sfbp + 9 * P;
-    // boundary-condition table [n_bc][4]: type, rho, u, v (16-byte aligned after the gradient)
-    constexpr int SG = kGradStride;
-    double *sbc = smem + (((3 * P1 + 2 * PT) * 8 + (9 * P + SG * P1) * (int)sizeof(R) + 15) / 16 * 16) / 8;
-    const gmem<int16_t> *ladj = gin(tl.ladj + (size_t)t * D * P1);
-    const gmem<int16_t> *lfc = gin(tl.lfc + (size_t)t * D * PT);
-    using T2 = typename std::conditional<S32, float2, double2>::type;   // tables
-    const gmem<T2> *lw, *frt;
-    if constexpr (S32) {
-        lw = gin(tl.lw32 + (size_t)t * D * P1);
-        frt = gin(tl.fr32 + (size_t)t * tl.nf_max * 3);
+    // LDS: W of the tile cells [3][PT] (faces on a boundary need it), the
+    // boundary table [n_bc]; then b and the slopes (x, y) [PA][9] of the tile and
+    // its first ring, cell by cell, and fbar+ [P][9], whose place the fluxes
+    // [8][PF] take in phase 3
+    double *const sW = smem;
+    WallBC *const sbc = reinterpret_cast<WallBC *>(sW + 3 * PT + (PT & 1));
+    R3 *const sr = reinterpret_cast<R3 *>(sbc + m.n_bc);
+    R *const sfb = reinterpret_cast<R *>(sr + 9 * PA);
+    R *const sphi = sfb;
+    const Factors<PM> c(m);
+
+    // ---- requests of all phases: the local cell id; what needs nothing loaded
+    // first; then the state at the cell id.  Indices are clamped with the tables'
+    // pitches, not the tile's own counts: every padded entry is a valid filler
+    // (cell 0, no neighbour, zero weight, empty face), so no request waits for
+    // the tile header, whose counts only mask what lanes without work read.
+    const int B = (int)blockDim.x;
+    // element i of a table (its base a scalar, the offset 32 bits)
+    auto ld = [](const auto *base, int i) {
+        using E = std::remove_const_t<std::remove_pointer_t<decltype(base)>>;
+        return *(const gmem<E> *)((const gmem<char> *)gin(base) + (uint32_t)i * (uint32_t)sizeof(E));
+    };
+    const int *const lgid = tl.lgid + (size_t)t * P;
+    const unsigned g1 = (unsigned)ld(lgid, tid < P ? tid : 0);
+    const int t2 = B + tid < P ? B + tid : 0;
+    const unsigned g2 = TWO ? (unsigned)ld(lgid, t2) : 0u;
+    const int ta = tid < PA ? tid : 0, tt = tid < PT ? tid : 0;
+    const int16_t *const ladj = tl.ladj + (size_t)t * D * PA, *const lfc = tl.lfc + (size_t)t * D * PT;
+    const T2 *lw, *fr;
+    if constexpr (PM == SDUGKS_FP64) {
+        lw = tl.lw + (size_t)t * D * PA;
+        fr = tl.fr + (size_t)t * PF * 3;
     } else {
-        lw = gin(tl.lw + (size_t)t * D * P1);
-        frt = gin(tl.fr + (size_t)t * tl.nf_max * 3);
+        lw = tl.lw32 + (size_t)t * D * PA;
+        fr = tl.fr32 + (size_t)t * PF * 3;
     }
-    const int PF = tl.nf_max;
-    // fbar+ from the cell variable (phase 1); the face step: reconstruction
-    // time and the coefficients of the face distribution (phase 3)
-    const R ra = (R)m.a, rb_ = (R)m.b, rc1 = (R)m.fc1, rbf = (R)m.fb, rdt = (R)m.dtr;
-    // ---- requests of all phases, in this order: the local cell ids and the
-    // face codes of the lanes; the adjacency, least-squares weights and
-    // boundary table, which need nothing loaded first; the phase-1 state at
-    // the cell ids; then the face records at the face codes.  Indices are
-    // clamped with the tables' pitches, not the tile's own counts: every
-    // padded entry is a valid filler (cell 0, no neighbour, zero weight, empty
-    // face), so no request waits for the tile header, whose counts only mask
-    // what lanes without work read.
-    const unsigned g1 = (unsigned)gin(tl.lgid)[(size_t)t * P + (tid < P ? tid : 0)];
-    const int lc3 = tid >> 2, sl3 = tid & 3;
-    const int sl3c = sl3 < D ? sl3 : D - 1;
-    const int lc3c = lc3 < PT ? lc3 : 0;
-    const int fc3 = lfc[sl3c * PT + lc3c];
-    __builtin_amdgcn_sched_barrier(0);
-    // phase 2 cell of this thread: in FP64, with two waves or more and at
-    // least twice as many threads as tile and first-ring cells, the two halves
-    // of the workgroup take the same cells, velocities 0..4 and 5..8 (in the
-    // deviation form the gradient is cheap enough that one half does it all)
-    const int half = (int)blockDim.x >> 1;
-    const bool split = !DEV && half >= 64 && P1 <= half;
-    const int c2 = split && tid >= half ? tid - half : tid;
-    const int t2 = c2 < P1 ? c2 : 0;
-    int la2[D];
-    R wx2[D], wy2[D];
+    int la[D], code[D];
+    T2 w[D];
 #pragma unroll
     for (int sl = 0; sl < D; sl++) {
-        la2[sl] = ladj[sl * P1 + t2];
-        const T2 w = lw[sl * P1 + t2];
-        wx2[sl] = (R)w.x;
-        wy2[sl] = (R)w.y;
+        la[sl] = ld(ladj, sl * PA + ta);
+        w[sl] = ld(lw, sl * PA + ta);
+        code[sl] = ld(lfc, sl * PT + tt);
     }
-    const int a3 = ladj[sl3c * P1 + lc3c];
+    struct Face {
+        int cells;
+        T2 ln, ra, rb;
+    };
+    auto face_of = [&](int f) {
+        const int k = f < PF ? f : 0;
+        return Face{ld(tl.fcell + (size_t)t * PF, k), ld(fr, k), ld(fr, PF + k), ld(fr, 2 * PF + k)};
+    };
+    const Face face1 = face_of(tid);
+    Face face2 = face1;
+    if constexpr (TWO) face2 = face_of(B + tid);
     const bool pb = tid < m.n_bc;
     const DevBC bcl = gin(m.bcs)[pb ? tid : 0];
     __builtin_amdgcn_sched_barrier(0);
-    const double r = gin(s.W)[g1], mu = gin(s.W)[(size_t)np + g1], mv = gin(s.W)[2 * (size_t)np + g1];
-    R fv[9];
+    const double r = gin(s.W)[g1], mu = gin(s.W)[np + g1], mv = gin(s.W)[2 * np + g1];
+    V fv[9];
 #pragma unroll
     for (int i = 0; i < 9; i++) {
-        if constexpr (S32) fv[i] = gin(s.f32)[(size_t)i * np + g1];
-        else fv[i] = gin(s.f)[(size_t)i * np + g1];
+        if constexpr (PM == SDUGKS_FP64) fv[i] = gin(s.f)[(size_t)i * np + g1];
+        else fv[i] = gin(s.f32)[(size_t)i * np + g1];
+    }
+    double W2[3] = {1.0, 0.0, 0.0};
+    V fv2[9];
+#pragma unroll
+    for (int i = 0; i < 9; i++) fv2[i] = 0;
+    if constexpr (TWO) {
+        for (int k = 0; k < 3; k++) W2[k] = gin(s.W)[k * np + g2];
+#pragma unroll
+        for (int i = 0; i < 9; i++) {
+            if constexpr (PM == SDUGKS_FP64) fv2[i] = gin(s.f)[(size_t)i * np + g2];
+            else fv2[i] = gin(s.f32)[(size_t)i * np + g2];
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
-    // the tile header: first cell and the counts of tile, first-ring and
-    // second-ring cells, for the masks of each phase
-    const gmem<int> *hd = gin(tl.hdr + 8 * t);
-    const int g0 = hd[0], nt = hd[1], na = nt + hd[2], nl = na + hd[3];
-    const bool p1 = tid < nl, p2 = c2 < na, p3 = lc3 < nt;
-#pragma unroll
-    for (int sl = 0; sl < D; sl++) la2[sl] = p2 ? la2[sl] : -1;
-    const int g3 = g0 + (p3 ? lc3 : 0);
-    const int la3 = (p3 && sl3 < D) ? a3 : -1;
-    // the lane's face: the record as seen from the lane's cell (l n, r_self,
-    // r_other), or from the other cell (-l n, r_other, r_self)
-    const int rec = fc3 >= 0 ? fc3 >> 1 : 0;
-    const T2 lnv = frt[rec], rav = frt[PF + rec], rbv = frt[2 * PF + rec];
-    const bool flip = (fc3 & 1) != 0;
-    const R lnx = flip ? -(R)lnv.x : (R)lnv.x, lny = flip ? -(R)lnv.y : (R)lnv.y;
-    const R rsx = (R)(flip ? rbv.x : rav.x), rsy = (R)(flip ? rbv.y : rav.y);
-    const R rox = (R)(flip ? rav.x : rbv.x), roy = (R)(flip ? rav.y : rbv.y);
+    // the tile header: counts of tile, first-ring and second-ring cells and faces
+    const gmem<int> *const hd = gin(tl.hdr + 8 * t);
+    const int nt = hd[1], na = nt + hd[2], nl = na + hd[3], nf = hd[4];
+    const bool p1 = tid < nl, p2 = tid < na, p4 = tid < nt;
+    const double dtv = gin(m.dtv)[p4 ? g1 : 0];
 
-    // ---- phase 1: macros and fbar+ of every local cell
-    if (pb) {
-        sbc[4 * tid] = (double)bcl.type;
-        sbc[4 * tid + 1] = bcl.rho;
-        sbc[4 * tid + 2] = bcl.u;
-        sbc[4 * tid + 3] = bcl.v;
+    // ---- phase 1
+    if (pb) sbc[tid] = {(double)bcl.type, bcl.rho, bcl.u, bcl.v};
+    if (p4) {
+        sW[tid] = r;
+        sW[PT + tid] = mu;
+        sW[2 * PT + tid] = mv;
     }
+    R fb[9];
     if (p1) {
-        const double ir = 1.0 / r;
-        const double ux = mu * ir, uy = mv * ir, uu = ux * ux + uy * uy;
-        if (tid < na) {
-            sW[tid] = r;
-            sW[P1 + tid] = ux;
-            sW[2 * P1 + tid] = uy;
-        }
-        if (tid < nt) {
-            sM[tid] = mu;
-            sM[PT + tid] = mv;
-        }
-        static_for<9>([&](auto I) {
-            constexpr int i = I;
-            const double fe = feq_c<cEx[i], cEy[i]>(cW[i], r, ux, uy, uu) - (DEV ? cW[i] * m.rho0 : 0.0);
-            // NEQ: fv is f - feq, and a + b = 1 (both schemes)
-            if constexpr (NEQ) sfbp[tid * 9 + i] = fe + ra * fv[i];
-            else sfbp[tid * 9 + i] = ra * fv[i] + rb_ * (R)fe;
-        });
-    }
-    __syncthreads();
-
-    // ---- phase 2: gradients of the tile and its first ring
-    if (p2) {
-        if (!split) gradient_cell<0, 9, D>(sfbp, ssg, sW, sbc, P1, c2, la2, wx2, wy2);
-        else if (tid < half) gradient_cell<0, 5, D>(sfbp, ssg, sW, sbc, P1, c2, la2, wx2, wy2);
-        else gradient_cell<5, 9, D>(sfbp, ssg, sW, sbc, P1, c2, la2, wx2, wy2);
-    }
-    __syncthreads();
-
-    // ---- phase 3: the face of each lane, per-cell sums, update
-    // the lane's velocities in the update: sl3, sl3 + 4 and, on lane 0, 8
-    // (the tile's own cells, just read in phase 1: cache hits)
-    double fo0, fo1, fo2;
-    if constexpr (S32) {
-        fo0 = gin(s.f32)[(size_t)sl3 * np + g3];
-        fo1 = gin(s.f32)[(size_t)(sl3 + 4) * np + g3];
-        fo2 = gin(s.f32)[(size_t)8 * np + g3];
-    } else {
-        fo0 = gin(s.f)[(size_t)sl3 * np + g3];
-        fo1 = gin(s.f)[(size_t)(sl3 + 4) * np + g3];
-        fo2 = gin(s.f)[(size_t)8 * np + g3];
-    }
-    const double dtv = gin(m.dtv)[g3];
-    R phi[9];
-    double g0s = 0.0, g1s = 0.0, g2s = 0.0;
+        cell_plus<PM>(m, c, r, mu, mv, fv, fb);
 #pragma unroll
-    for (int i = 0; i < 9; i++) phi[i] = 0;
-    if (la3 != -1) {
-        const int lc = lc3;
-        R fbar[9];
-        if (la3 >= 0) {
-            // upwind side by the sign of e.n; exact tie: mean of both sides
-            const int la = la3;
-            static_for<9>([&](auto I) {
-                constexpr int i = I, EX = cEx[i], EY = cEy[i];
-                const R sn = cdot<EX, EY>(lnx, lny);
-                const R rs = sfbp[lc * 9 + i] + csub<EX>(rsx, rdt) * ssg[lc * SG + i]
-                             + csub<EY>(rsy, rdt) * ssg[lc * SG + 9 + i];
-                const R ro = sfbp[la * 9 + i] + csub<EX>(rox, rdt) * ssg[la * SG + i]
-                             + csub<EY>(roy, rdt) * ssg[la * SG + 9 + i];
-                const R up = sn > (R)0 ? rs : ro;
-                fbar[i] = sn == (R)0 ? (R)0.5 * (rs + ro) : up;
-            });
-        } else {
-            const double r = sW[lc], ux = sW[P1 + lc], uy = sW[2 * P1 + lc];
-            double rb, ub, vb;
-            boundary_state_t(sbc, -2 - la3, r, ux, uy, rb, ub, vb);
-            const double uu = ux * ux + uy * uy, uub = ub * ub + vb * vb;
-            static_for<9>([&](auto I) {
-                constexpr int i = I, EX = cEx[i], EY = cEy[i];
-                const R sn = cdot<EX, EY>(lnx, lny);
-                const R sx = ssg[lc * SG + i], sy = ssg[lc * SG + 9 + i];
-                const R fb = sfbp[lc * 9 + i];
-                const R inner = fb + csub<EX>(rsx, rdt) * sx + csub<EY>(rsy, rdt) * sy;
-                // incoming: the boundary state's fbar+ carried to the foot point
-                const R gb = (R)(feq_c<EX, EY>(cW[i], rb, ub, vb, uub) - feq_c<EX, EY>(cW[i], r, ux, uy, uu)) + fb;
-                fbar[i] = sn >= (R)0 ? inner : gb - rdt * cdot<EX, EY>(sx, sy);
-            });
+        for (int i = 0; i < 9; i++) sfb[tid * 9 + i] = fb[i];
+    }
+    if (TWO && B + tid < nl) {
+        R fb2[9];
+        cell_plus<PM>(m, c, W2[0], W2[1], W2[2], fv2, fb2);
+#pragma unroll
+        for (int i = 0; i < 9; i++) sfb[t2 * 9 + i] = fb2[i];
+    }
+    __syncthreads();
+
+    // ---- phase 2
+    if (p2) {
+        R gx[9], gy[9], b[9];
+#pragma unroll
+        for (int i = 0; i < 9; i++) { gx[i] = 0; gy[i] = 0; }
+        // neighbours first, without a branch (an empty slot or a boundary point
+        // reads the cell itself, whose difference is zero), so that all reads are
+        // in flight together; then the few boundary points
+        bool wall = false;
+#pragma unroll
+        for (int sl = 0; sl < D; sl++) {
+            const int nb = la[sl] >= 0 ? la[sl] : tid;
+            const R wx = (R)w[sl].x, wy = (R)w[sl].y;
+            wall = wall || la[sl] < -1;
+#pragma unroll
+            for (int i = 0; i < 9; i++) {
+                const R df = sfb[nb * 9 + i] - fb[i];
+                gx[i] = fma_(wx, df, gx[i]);
+                gy[i] = fma_(wy, df, gy[i]);
+            }
+        }
+        if (wall) {
+#pragma unroll
+            for (int sl = 0; sl < D; sl++) {
+                if (la[sl] >= -1) continue;
+                R df[9];
+                wall_diff<PM>(m, sbc[-2 - la[sl]], r, mu, mv, df);
+#pragma unroll
+                for (int i = 0; i < 9; i++) { gx[i] = fma_((R)w[sl].x, df[i], gx[i]); gy[i] = fma_((R)w[sl].y, df[i], gy[i]); }
+            }
+        }
+        carry_back(c.dt, fb, gx, gy, b);
+#pragma unroll
+        for (int i = 0; i < 9; i++) sr[tid * 9 + i] = R3{b[i], gx[i], gy[i]};
+    }
+    __syncthreads();
+
+    // ---- phase 3
+    auto face_fluxes = [&](int f, const Face &face) {
+        const int c0 = face.cells & 0xffff, c1 = face.cells >> 16;      // c1 < 0: boundary entry -2 - c1
+        const R lx = (R)face.ln.x, ly = (R)face.ln.y, ax = (R)face.ra.x, ay = (R)face.ra.y;
+        const bool inner = c1 >= 0;
+        const int c2 = inner ? c1 : c0;
+        const R bx = inner ? (R)face.rb.x : ax, by = inner ? (R)face.rb.y : ay;
+        auto at = [&](int cell, R x, R y, int i) {
+            const R3 v = sr[cell * 9 + i];
+            return fma_(y, v.y, fma_(x, v.x, v.b));
+        };
+        const R f0 = (R)0.5 * (at(c0, ax, ay, 0) + at(c2, bx, by, 0));
+        R fp[4], fm[4], sn[4];
+        bool special = !inner;
+        static_for<4>([&](auto K) {
+            constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
+            sn[k] = cdot<cEx[p], cEy[p]>(lx, ly);
+            special = special || sn[k] == (R)0;
+            // of the pair, out leaves the first cell and in the second
+            const bool up = sn[k] > (R)0;
+            const int io = up ? p : q;
+            const R out = at(c0, ax, ay, io), in = at(c2, bx, by, p + q - io);
+            fp[k] = up ? out : in;
+            fm[k] = up ? in : out;
+        });
+        if (special) {
+            if (!inner) {
+                // entering through a boundary: the boundary state's fbar+ carried to the
+                // foot point; leaving or along it: the cell's own value
+                R df[9];
+                wall_diff<PM>(m, sbc[-2 - c1], sW[c0], sW[PT + c0], sW[2 * PT + c0], df);
+                static_for<4>([&](auto K) {
+                    constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
+                    const R ip = sr[c0 * 9 + p].b + df[p], iq = sr[c0 * 9 + q].b + df[q];
+                    fm[k] = sn[k] > (R)0 ? iq : fm[k];
+                    fp[k] = sn[k] < (R)0 ? ip : fp[k];
+                });
+            } else {
+                // along the face: the mean of both sides
+                static_for<4>([&](auto K) {
+                    constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
+                    const R mp = (R)0.5 * (at(c0, ax, ay, p) + at(c2, bx, by, p));
+                    const R mq = (R)0.5 * (at(c0, ax, ay, q) + at(c2, bx, by, q));
+                    fp[k] = sn[k] == (R)0 ? mp : fp[k];
+                    fm[k] = sn[k] == (R)0 ? mq : fm[k];
+                });
+            }
         }
         // face macros (deviations in DEV: rho_f = rho0 + sum, momentum unchanged)
-        R rsum = fbar[0], mx = 0, my = 0;
-        static_for<9>([&](auto I) {
-            constexpr int i = I;
-            if constexpr (i > 0) rsum += fbar[i];
-            if constexpr (cEx[i] != 0) mx += cmul<cEx[i]>(fbar[i]);
-            if constexpr (cEy[i] != 0) my += cmul<cEy[i]>(fbar[i]);
-        });
-        const R rf = DEV ? (R)m.rho0 + rsum : rsum;
-        const R irf = (R)1 / rf;
+        const R rsum = f0 + (((fp[0] + fm[0]) + (fp[1] + fm[1])) + ((fp[2] + fm[2]) + (fp[3] + fm[3])));
+        const R d2 = fp[2] - fm[2], d3 = fp[3] - fm[3];
+        const R mx = (fp[0] - fm[0]) + (d2 - d3), my = (fp[1] - fm[1]) + (d2 + d3);
+        const R rf = PM == SDUGKS_FP32DEV ? (R)m.rho0 + rsum : rsum;
+        R irf;
+        if constexpr (PM == SDUGKS_FP32DEV) irf = (R)1 / rf;
+        else irf = recip(rf);
         const R uf = mx * irf, vf = my * irf;
-        const R uu = uf * uf + vf * vf;
-        static_for<9>([&](auto I) {
-            constexpr int i = I, EX = cEx[i], EY = cEy[i];
-            const R sn = cdot<EX, EY>(lnx, lny);
-            R fe;
-            if constexpr (DEV) {
-                const R eu = cdot<EX, EY>(uf, vf);
-                fe = (R)cW[i] * (rsum + rf * ((R)3 * eu + (R)4.5 * eu * eu - (R)1.5 * uu));
-            } else {
-                fe = feq_c<EX, EY>((R)cW[i], rf, uf, vf, uu);
-            }
-            phi[i] = sn * (rc1 * (fbar[i] + rbf * fe));
-            g0s += (double)phi[i];
-            if constexpr (EX != 0) g1s += cmul<EX>((double)phi[i]);
-            if constexpr (EY != 0) g2s += cmul<EY>((double)phi[i]);
+        const R B = fma_((R)-1.5, fma_(mx, uf, my * vf), rsum);
+        const R k1 = c.c1 * c.k1, k5 = c.c1 * c.k5;
+        // fluxes along n of the pair (p, q): e_q = -e_p
+        auto flux = [&](int k, R K, R dm, R du) {
+            const R S = fma_((R)4.5 * dm, du, B);
+            sphi[(2 * k) * PF + f] = sn[k] * fma_(K, fma_((R)3, dm, S), c.c1 * fp[k]);
+            sphi[(2 * k + 1) * PF + f] = -sn[k] * fma_(K, fma_((R)-3, dm, S), c.c1 * fm[k]);
+        };
+        flux(0, k1, mx, uf);
+        flux(1, k1, my, vf);
+        flux(2, k5, mx + my, uf + vf);
+        flux(3, k5, my - mx, vf - uf);
+    };
+    if (tid < nf) face_fluxes(tid, face1);
+    if (TWO && B + tid < nf) face_fluxes(B + tid, face2);
+    __syncthreads();
+
+    // ---- phase 4
+    if (!p4) return;
+    Outflow o;
+#pragma unroll
+    for (int i = 0; i < 9; i++) o.F[i] = 0.0;
+#pragma unroll
+    for (int sl = 0; sl < D; sl++) {
+        if (code[sl] < 0) continue;
+        const R *const ph = sphi + (code[sl] >> 1);
+        const double sign = (code[sl] & 1) ? -1.0 : 1.0;        // the record as seen from the other cell
+        static_for<8>([&](auto I) {
+            constexpr int i = cPair[I / 2][I % 2];
+            o.F[i] = fma_(sign, (double)ph[I * PF], o.F[i]);
         });
     }
+    double G[3] = {0.0, 0.0, 0.0}, Wn[3];
+    if (lagged)
+        for (int k = 0; k < 3; k++) G[k] = gin(s.G)[k * np + g1];
+    V v[9];
+    cell_update<PM>(m, lagged, dtv, r, mu, mv, o, fv, G, Wn[0], Wn[1], Wn[2], v);
+#pragma unroll
+    for (int k = 0; k < 3; k++) gout(s.Wo)[k * np + g1] = Wn[k];
 #pragma unroll
     for (int i = 0; i < 9; i++) {
-        if constexpr (PM == 1) phi[i] = lane_sum4_comp(phi[i]);
-        else phi[i] = lane_sum4(phi[i]);
+        if constexpr (PM == SDUGKS_FP64) gout(s.fo)[(size_t)i * np + g1] = v[i];
+        else gout(s.fo32)[(size_t)i * np + g1] = v[i];
     }
-    g0s = lane_sum4(g0s);
-    g1s = lane_sum4(g1s);
-    g2s = lane_sum4(g2s);
-    if (p3) {
-        const int lc = lc3, g = g3;
-        double G0 = g0s, G1 = g1s, G2 = g2s;
-        if (lagged) { G0 = gin(s.G)[g]; G1 = gin(s.G)[np + g]; G2 = gin(s.G)[2 * np + g]; }
-        const double rn = sW[lc] - dtv * G0;
-        const double mxn = sM[lc] - dtv * G1;
-        const double myn = sM[PT + lc] - dtv * G2;
-        if (sl3 == 0) gout(s.Wo)[g] = rn;
-        if (sl3 == 1) gout(s.Wo)[np + g] = mxn;
-        if (sl3 == 2) gout(s.Wo)[2 * np + g] = myn;
-        if (lagged) {
-            if (sl3 == 0) gout(s.Go)[g] = g0s;
-            if (sl3 == 1) gout(s.Go)[np + g] = g1s;
-            if (sl3 == 2) gout(s.Go)[2 * np + g] = g2s;
-        }
-        const double irn = 1.0 / rn;
-        const double un = mxn * irn, vn = myn * irn, uun = un * un + vn * vn;
-        const double inv = m.inv1l, lam = m.lam;
-        // this lane's velocities: i0 = sl3 (rest, +x, +y, -x) and i1 = sl3 + 4
-        // (-y, (1,1), (-1,1), (-1,-1)); their e.u, weights and fluxes
-        const double eu0 = sl3 == 0 ? 0.0 : (sl3 == 1 ? un : (sl3 == 2 ? vn : -un));
-        const double eu1 = sl3 == 0 ? -vn : (sl3 == 1 ? un + vn : (sl3 == 2 ? vn - un : -(un + vn)));
-        const double w0 = sl3 == 0 ? cW[0] : cW[1], w1 = sl3 == 0 ? cW[4] : cW[5];
-        const double F0 = sl3 == 0 ? phi[0] : (sl3 == 1 ? phi[1] : (sl3 == 2 ? phi[2] : phi[3]));
-        const double F1 = sl3 == 0 ? phi[4] : (sl3 == 1 ? phi[5] : (sl3 == 2 ? phi[6] : phi[7]));
-        const double base = 1.0 - 1.5 * uun;
-        const int i0 = sl3, i1 = sl3 + 4;
-        if constexpr (NEQ) {
-            // f^n of this lane's velocities = feq(W^n) + the stored part
-            const double ro = sW[lc], uo = sW[P1 + lc], vo = sW[2 * P1 + lc];
-            const double bo = 1.0 - 1.5 * (uo * uo + vo * vo);
-            const double e0 = sl3 == 0 ? 0.0 : (sl3 == 1 ? uo : (sl3 == 2 ? vo : -uo));
-            const double e1 = sl3 == 0 ? -vo : (sl3 == 1 ? uo + vo : (sl3 == 2 ? vo - uo : -(uo + vo)));
-            fo0 += w0 * ro * (bo + e0 * (3.0 + 4.5 * e0));
-            fo1 += w1 * ro * (bo + e1 * (3.0 + 4.5 * e1));
-            if (sl3 == 0) fo2 += feq_c<cEx[8], cEy[8]>(cW[8], ro, uo, vo, uo * uo + vo * vo);
-        }
-        const double fe0 = w0 * rn * (base + eu0 * (3.0 + 4.5 * eu0)) - (DEV ? w0 * m.rho0 : 0.0);
-        const double fe1 = w1 * rn * (base + eu1 * (3.0 + 4.5 * eu1)) - (DEV ? w1 * m.rho0 : 0.0);
-        double v0, v1;
-        if (m.scheme == 0) {
-            v0 = (fo0 - dtv * F0 + lam * fe0) * inv;
-            v1 = (fo1 - dtv * F1 + lam * fe1) * inv;
-        } else {
-            // the original scheme: ft^{n+1} = (4/3) fbar+ - (1/3) ft - dt/V F
-            v0 = (4.0 / 3.0) * (double)sfbp[lc * 9 + i0] - (1.0 / 3.0) * fo0 - dtv * F0;
-            v1 = (4.0 / 3.0) * (double)sfbp[lc * 9 + i1] - (1.0 / 3.0) * fo1 - dtv * F1;
-        }
-        if constexpr (NEQ) { v0 -= fe0; v1 -= fe1; }          // store f^{n+1} - feq(W^{n+1})
-        if constexpr (S32) { gout(s.fo32)[(size_t)i0 * np + g] = (float)v0; gout(s.fo32)[(size_t)i1 * np + g] = (float)v1; }
-        else { gout(s.fo)[(size_t)i0 * np + g] = v0; gout(s.fo)[(size_t)i1 * np + g] = v1; }
-        if (sl3 == 0) {
-            const double fe2 = feq_c<cEx[8], cEy[8]>(cW[8], rn, un, vn, uun) - (DEV ? cW[8] * m.rho0 : 0.0);
-            double v2;
-            if (m.scheme == 0) {
-                v2 = (fo2 - dtv * (double)phi[8] + lam * fe2) * inv;
-            } else {
-                v2 = (4.0 / 3.0) * (double)sfbp[lc * 9 + 8] - (1.0 / 3.0) * fo2 - dtv * (double)phi[8];
-            }
-            if constexpr (NEQ) v2 -= fe2;
-            if constexpr (S32) gout(s.fo32)[(size_t)8 * np + g] = (float)v2;
-            else gout(s.fo)[(size_t)8 * np + g] = v2;
-        }
-    }
+    if (lagged)
+        for (int k = 0; k < 3; k++) gout(s.Go)[k * np + g1] = G[k];
 }
 
 // Workgroups are dealt round-robin to the XCDs: block b runs on XCD b % 8.
@@ -394,15 +331,19 @@ __device__ __forceinline__ int xcd_tile(int n)
     return (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
 }
 
+// Waves on a SIMD that the registers are bound to allow.
+template <int PM, bool TWO>
+constexpr int kTiledWaves = PM == SDUGKS_FP32DEV ? 4 : (TWO ? 2 : 3);
+
 // One block per tile: the tile of this block, XCD by XCD in contiguous ranges
 // (xcd_range_start).  It follows from the block index and the grid size
 // alone, so the first requests wait for nothing but the table pointers.
-template <int D, int PM>
-__global__ void __launch_bounds__(256) k_step_tiled(DevMesh m, DevTiles tl, DevState s, int lagged)
+template <int D, int PM, bool TWO>
+__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_tiled(DevMesh m, DevTiles tl, DevState s, int lagged)
 {
     const int x = (int)(blockIdx.x % kXcds);
     const int t = xcd_range_start((int)gridDim.x, x) + (int)(blockIdx.x / kXcds);
-    step_tile<D, PM>(m, tl, s, lagged, t);
+    step_tile<D, PM, TWO>(m, tl, s, lagged, t);
 }
 
 // Batched step: the tiles of all instances form one sequence; the grid covers
@@ -413,8 +354,8 @@ __global__ void __launch_bounds__(256) k_step_tiled(DevMesh m, DevTiles tl, DevS
 // memory is reached through global-address-space pointers (gin, gout in
 // step_tile): the members' pointers come from their records, not from
 // kernel arguments.
-template <int D, int PM>
-__global__ void __launch_bounds__(256) k_step_batch(BatchTable tab, int parity)
+template <int D, int PM, bool TWO>
+__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_batch(BatchTable tab, int parity)
 {
     // the slot's (member, tile) as one 8-byte load, so that the tile index
     // does not wait for the exit test on the member
@@ -428,25 +369,15 @@ __global__ void __launch_bounds__(256) k_step_batch(BatchTable tab, int parity)
     const BatchInst &in = tab.inst[member < 0 ? 0 : member];
     const DevMesh m = in.m;
     const DevTiles tl = in.t;
-    const bool sw = ((in.parity0 ^ parity) & 1) != 0;
-    void *const f0 = in.f[0], *const f1 = in.f[1];
-    double *const W0 = in.W[0], *const W1 = in.W[1], *const G0 = in.G[0], *const G1 = in.G[1];
-    DevState s;
-    s.W = sw ? W1 : W0; s.G = sw ? G1 : G0; s.Wo = sw ? W0 : W1; s.Go = sw ? G0 : G1;
-    void *const fi = sw ? f1 : f0, *const fo = sw ? f0 : f1;
-    s.f = reinterpret_cast<const double *>(fi);
-    s.fo = reinterpret_cast<double *>(fo);
-    s.f32 = reinterpret_cast<const float *>(fi);
-    s.fo32 = reinterpret_cast<float *>(fo);
     if (member < 0) return;
-    step_tile<D, PM>(m, tl, s, in.lagged, tile);
+    step_tile<D, PM, TWO>(m, tl, batch_state(in, parity), in.lagged, tile);
 }
 
 }  // namespace
 
 size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc)
 {
-    return tile_lds_bytes(t.nl_max, t.na_max, t.nt_max, n_bc, mode == 1 ? sizeof(float) : sizeof(double));
+    return tile_lds_bytes(t.nl_max, t.na_max, t.nt_max, t.nf_max, n_bc, mode == 1 ? sizeof(float) : sizeof(double));
 }
 
 static unsigned step_tiled_grid(const DevTiles &t) { return (unsigned)t.n_tiles; }
@@ -458,7 +389,10 @@ hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState
 {
     const size_t lds = step_tiled_lds_bytes(t, mode, m.n_bc);
     const dim3 grid(step_tiled_grid(t)), blk(block);
-#define SDG_TILED(DD, PP) return emit(&k_step_tiled<DD, PP>, grid, blk, lds, st, gc, m, t, s, lagged)
+    const bool two = step_tiled_two(t, block);
+#define SDG_TILED(DD, PP) \
+    return two ? emit(&k_step_tiled<DD, PP, true>, grid, blk, lds, st, gc, m, t, s, lagged) \
+               : emit(&k_step_tiled<DD, PP, false>, grid, blk, lds, st, gc, m, t, s, lagged)
     if (m.D <= 3) {
         if (mode == 1) SDG_TILED(3, 1);
         if (mode == 2) SDG_TILED(3, 2);
@@ -470,11 +404,13 @@ hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState
 #undef SDG_TILED
 }
 
-hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, int parity, int cap_tiles, size_t lds,
+hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds,
                              int block, hipStream_t st, GraphChain *gc)
 {
     const dim3 grid((unsigned)batch_grid(cap_tiles)), blk(block);
-#define SDG_BATCH(DD, PP) return emit(&k_step_batch<DD, PP>, grid, blk, lds, st, gc, tab, parity)
+#define SDG_BATCH(DD, PP) \
+    return two ? emit(&k_step_batch<DD, PP, true>, grid, blk, lds, st, gc, tab, parity) \
+               : emit(&k_step_batch<DD, PP, false>, grid, blk, lds, st, gc, tab, parity)
     if (D <= 3) {
         if (mode == 1) SDG_BATCH(3, 1);
         if (mode == 2) SDG_BATCH(3, 2);
