@@ -48,12 +48,20 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t np = 0;
     size_t off_f[2]{}, off_W[2]{}, off_G[2]{}, off_fbp = 0, off_sg = 0, off_snap = 0;
-    size_t off_nbr = 0, off_geo = 0, off_ainv = 0, off_dtv = 0, off_area = 0, off_bft = 0, off_bcs = 0;
+    size_t off_nbr = 0, off_geo = 0, off_ainv = 0, off_dtv = 0, off_area = 0, off_bft = 0, off_bcs = 0, off_iperm = 0;
     size_t off_part = 0, off_out = 0, total = 0;
     size_t off_thdr = 0, off_lgid = 0, off_ladj = 0, off_lfc = 0, off_fcell = 0, off_frec = 0, off_lw = 0;
     size_t off_bq_hdr = 0, off_bq_nb = 0, off_bq_w = 0, off_bq_geo = 0, off_bq_out = 0, off_bq_sum = 0;
     size_t off_ccol = 0, off_crow = 0, off_cside = 0;
 };
+
+// Whether the internal cell order is the caller's.
+bool same_order(const MeshBuild &mb)
+{
+    for (int32_t k = 0; k < mb.nc; k++)
+        if (mb.perm[k] != k) return false;
+    return true;
+}
 
 // What the three step forms need: the two-kernel step keeps fbar+ and its
 // gradient in memory with per-cell neighbour lists, inverse normal matrices
@@ -96,6 +104,7 @@ Layout make_layout(const MeshBuild &mb, int precision)
         L.off_bft = take(std::max<size_t>(1, mb.n_bfaces) * sizeof(int32_t));
     }
     L.off_snap = take(2 * row);
+    if (!same_order(mb)) L.off_iperm = take(mb.iperm.size() * sizeof(int32_t));
     if (mb.n_tiles == 0) L.off_geo = take(6 * (size_t)mb.D * row);   // two-kernel step: FP64 only
     L.off_dtv = take(row);
     L.off_area = take(row);
@@ -135,6 +144,7 @@ struct sdugks_s {
     DevCart dc{};
     DevBnd bq{};
     CartBlock blk{};             // boxes of the form with several steps per launch
+    StateLayout io{};            // the state's layout, for moving it to and from the caller's order
     int kmax = 1;                // steps a launch takes at most (1: the marching or general step)
     bool whole = false;          // one box holds the mesh
     double *host4 = nullptr;     // pinned, 4 doubles
@@ -613,99 +623,64 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         d.dtr = hh; d.fb = hh / (2.0 * tau); d.fc1 = 2.0 * tau / (2.0 * tau + hh);
     }
     d.dt = dt;
+    h->io = {(int32_t)np, h->precision, nullptr, h->rho0, h->scheme == SDUGKS_SCHEME_ORIGINAL ? dt / (2.0 * tau) : 0.0};
+    if (!same_order(mb)) {
+        if (hipMemcpy(h->at<int32_t>(L.off_iperm), mb.iperm.data(), nc * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
+            return cleanup(fail(SDUGKS_EHIP, "upload of the cell order failed"));
+        h->io.iperm = h->at<int32_t>(L.off_iperm);
+    }
     // initial state: uniform equilibrium, G = 0, snapshot = initial velocity
-    {
-        std::vector<double> f(9 * nc), W(3 * nc), G(3 * nc, 0.0);
-        for (size_t c = 0; c < nc; c++) {
-            for (int i = 0; i < 9; i++) f[c * 9 + i] = feq_host(i, prm->rho0, prm->u0, prm->v0);
-            W[3 * c] = prm->rho0; W[3 * c + 1] = prm->rho0 * prm->u0; W[3 * c + 2] = prm->rho0 * prm->v0;
-        }
-        *out = h;
-        // set_state expects caller order; the uniform state is order-free
-        rc = sdugks_set_state(h, f.data(), W.data(), G.data());
-        if (rc) { *out = nullptr; return cleanup(rc); }
+    // (the original scheme's variable of an equilibrium is f itself)
+    double f9[9];
+    const double W3[3] = {prm->rho0, prm->rho0 * prm->u0, prm->rho0 * prm->v0};
+    for (int i = 0; i < 9; i++) {
+        const double w = i == 0 ? 4.0 / 9 : (i < 5 ? 1.0 / 9 : 1.0 / 36), fe = feq_host(i, prm->rho0, prm->u0, prm->v0);
+        f9[i] = h->precision == SDUGKS_FP64 ? fe : (h->precision == SDUGKS_FP32DEV ? fe - w * h->rho0 : 0.0);
+    }
+    if (launch_set_uniform((int)nc, (int)np, f9, W3, dev ? nullptr : h->at<double>(L.off_f[0]),
+                           dev ? h->at<float>(L.off_f[0]) : nullptr, h->at<double>(L.off_W[0]), h->at<double>(L.off_G[0]),
+                           h->at<double>(L.off_snap), h->stream) != hipSuccess ||
+        hipStreamSynchronize(h->stream) != hipSuccess)
+        return cleanup(fail(SDUGKS_EHIP, "setting the initial state failed"));
+    *out = h;
+    return SDUGKS_OK;
+}
+
+namespace {
+
+// Move cells of `width` values between the caller's array and the rows of the
+// state through the f rows that the next step writes (free until then), as many
+// cells at a time as fit there.
+int move_state(sdugks_t *h, StateMove move, int width, double *host, size_t off_rows, double *snap)
+{
+    const size_t nc = h->mb.nc, bytes = 9 * h->L.np * (h->dev32() ? sizeof(float) : sizeof(double));
+    double *const stage = h->at<double>(h->L.off_f[h->cur ^ 1]);
+    const size_t most = bytes / (width * sizeof(double));
+    const bool put = move == kPutRows3 || move == kPutF;
+    const double *W = h->at<double>(h->L.off_W[h->cur]);
+    for (size_t c0 = 0; c0 < nc; c0 += most) {
+        const size_t n = std::min(most, nc - c0), size = n * width * sizeof(double);
+        if (put) HIPCHK(hipMemcpyAsync(stage, host + c0 * width, size, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(launch_state_io(move, h->io, (int)c0, (int)n, W, h->base + off_rows, snap, stage, h->stream));
+        if (!put) HIPCHK(hipMemcpyAsync(host + c0 * width, stage, size, hipMemcpyDeviceToHost, h->stream));
+        // the caller's memory is free, and the staging rows may be written again
+        HIPCHK(hipStreamSynchronize(h->stream));
     }
     return SDUGKS_OK;
 }
 
-// The original scheme stores ft = f - (dt/2) Omega = (1 + k) f - k feq(W),
-// k = dt/(2 tau); inverse f = (ft + k feq(W)) / (1 + k).  Caller order, in place.
-static void tilde_convert(double *f, const double *W, size_t nc, double k, bool inverse)
-{
-    for (size_t c = 0; c < nc; c++) {
-        const double r = W[3 * c], u = W[3 * c + 1] / r, v = W[3 * c + 2] / r;
-        for (int i = 0; i < 9; i++) {
-            const double fe = feq_host(i, r, u, v);
-            double &x = f[c * 9 + i];
-            x = inverse ? (x + k * fe) / (1.0 + k) : (1.0 + k) * x - k * fe;
-        }
-    }
-}
+}  // namespace
 
 int sdugks_set_state(sdugks_t *h, const double *f, const double *W, const double *G)
 {
     if (!h) return fail(SDUGKS_EINVAL, "null handle");
     HIPCHK(hipSetDevice(h->device));
-    const size_t nc = h->mb.nc, np = h->L.np;
-    std::vector<double> ft, Wc;
-    const bool neq = h->precision == SDUGKS_FP32NEQ;
-    if (f && (h->scheme == SDUGKS_SCHEME_ORIGINAL || neq)) {
-        // the macros that go with f: the new ones, else the stored ones
-        Wc.resize(3 * nc);
-        if (W) std::copy(W, W + 3 * nc, Wc.begin());
-        else if (int r0 = sdugks_get_state(h, nullptr, Wc.data(), nullptr)) return r0;
-    }
-    if (f && h->scheme == SDUGKS_SCHEME_ORIGINAL) {
-        ft.assign(f, f + 9 * nc);
-        tilde_convert(ft.data(), Wc.data(), nc, h->mb.dt / (2.0 * h->mb.tau), false);
-        f = ft.data();
-    }
     const Layout &L = h->L;
-    std::vector<double> buf(9 * np, 0.0);
-    auto put = [&](const double *src, int rows, size_t off) -> int {
-        std::fill(buf.begin(), buf.end(), 0.0);
-        for (size_t k = 0; k < nc; k++) {
-            size_t c = h->mb.perm[k];
-            for (int r = 0; r < rows; r++) buf[r * np + k] = src[c * rows + r];
-        }
-        HIPCHK(hipMemcpyAsync(h->base + off, buf.data(), rows * np * sizeof(double), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        return SDUGKS_OK;
-    };
+    // W first: f is stored relative to the macros that go with it, the new ones or else the stored ones
     int rc;
-    if (f && h->dev32()) {
-        // FP32 storage: f - w_i rho0 (FP32DEV) or f - feq(W) (FP32NEQ)
-        static const double w[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
-        std::vector<float> b32(9 * np, 0.0f);
-        for (size_t k = 0; k < nc; k++) {
-            size_t c = h->mb.perm[k];
-            for (int i = 0; i < 9; i++) {
-                double ref = w[i] * h->rho0;
-                if (neq) {
-                    const double r = Wc[3 * c];
-                    ref = feq_host(i, r, Wc[3 * c + 1] / r, Wc[3 * c + 2] / r);
-                }
-                b32[i * np + k] = (float)(f[c * 9 + i] - ref);
-            }
-        }
-        HIPCHK(hipMemcpyAsync(h->base + L.off_f[h->cur], b32.data(), 9 * np * sizeof(float), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-    } else if (f && (rc = put(f, 9, L.off_f[h->cur]))) {
-        return rc;
-    }
-    if (W) {
-        if ((rc = put(W, 3, L.off_W[h->cur]))) return rc;
-        // snapshot of the residual = this velocity field
-        std::vector<double> snap(2 * np, 0.0);
-        for (size_t k = 0; k < nc; k++) {
-            size_t c = h->mb.perm[k];
-            snap[k] = W[3 * c + 1] / W[3 * c];
-            snap[np + k] = W[3 * c + 2] / W[3 * c];
-        }
-        HIPCHK(hipMemcpyAsync(h->base + L.off_snap, snap.data(), 2 * np * sizeof(double), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-    }
-    if (G && (rc = put(G, 3, L.off_G[h->cur]))) return rc;
+    if (W && (rc = move_state(h, kPutRows3, 3, const_cast<double *>(W), L.off_W[h->cur], h->at<double>(L.off_snap)))) return rc;
+    if (f && (rc = move_state(h, kPutF, 9, const_cast<double *>(f), L.off_f[h->cur], nullptr))) return rc;
+    if (G && (rc = move_state(h, kPutRows3, 3, const_cast<double *>(G), L.off_G[h->cur], nullptr))) return rc;
     h->diverged = false;
     return SDUGKS_OK;
 }
@@ -715,50 +690,13 @@ int sdugks_get_state(sdugks_t *h, double *f, double *W, double *G)
     if (!h) return fail(SDUGKS_EINVAL, "null handle");
     HIPCHK(hipSetDevice(h->device));
     HIPCHK(hipStreamSynchronize(h->stream));
-    const size_t nc = h->mb.nc, np = h->L.np;
     const Layout &L = h->L;
-    std::vector<double> buf(9 * np);
-    auto get = [&](double *dst, int rows, size_t off) -> int {
-        HIPCHK(hipMemcpyAsync(buf.data(), h->base + off, rows * np * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        for (size_t k = 0; k < nc; k++) {
-            size_t c = h->mb.perm[k];
-            for (int r = 0; r < rows; r++) dst[c * rows + r] = buf[r * np + k];
-        }
-        return SDUGKS_OK;
-    };
     int rc;
-    const bool neq = h->precision == SDUGKS_FP32NEQ;
-    std::vector<double> Wc;
-    if (f && (neq || h->scheme == SDUGKS_SCHEME_ORIGINAL)) {
-        Wc.resize(3 * nc);
-        if ((rc = get(Wc.data(), 3, L.off_W[h->cur]))) return rc;
-    }
-    if (f && h->dev32()) {
-        // FP32 storage: f = w_i rho0 (FP32DEV) or feq(W) (FP32NEQ) + stored part
-        static const double w[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
-        std::vector<float> b32(9 * np);
-        HIPCHK(hipMemcpyAsync(b32.data(), h->base + L.off_f[h->cur], 9 * np * sizeof(float), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        for (size_t k = 0; k < nc; k++) {
-            size_t c = h->mb.perm[k];
-            for (int i = 0; i < 9; i++) {
-                double ref = w[i] * h->rho0;
-                if (neq) {
-                    const double r = Wc[3 * c];
-                    ref = feq_host(i, r, Wc[3 * c + 1] / r, Wc[3 * c + 2] / r);
-                }
-                f[c * 9 + i] = ref + (double)b32[i * np + k];
-            }
-        }
-    } else if (f && (rc = get(f, 9, L.off_f[h->cur]))) {
-        return rc;
-    }
-    if (W && (rc = get(W, 3, L.off_W[h->cur]))) return rc;
-    if (f && h->scheme == SDUGKS_SCHEME_ORIGINAL) tilde_convert(f, Wc.data(), nc, h->mb.dt / (2.0 * h->mb.tau), true);
+    if (f && (rc = move_state(h, kGetF, 9, f, L.off_f[h->cur], nullptr))) return rc;
+    if (W && (rc = move_state(h, kGetRows3, 3, W, L.off_W[h->cur], nullptr))) return rc;
     if (G) {
-        if (h->macro == SDUGKS_MACRO_LAGGED) { if ((rc = get(G, 3, L.off_G[h->cur]))) return rc; }
-        else std::fill(G, G + 3 * nc, 0.0);
+        if (h->macro != SDUGKS_MACRO_LAGGED) std::fill(G, G + 3 * (size_t)h->mb.nc, 0.0);
+        else if ((rc = move_state(h, kGetRows3, 3, G, L.off_G[h->cur], nullptr))) return rc;
     }
     return SDUGKS_OK;
 }
@@ -798,14 +736,15 @@ int sdugks_set_macros(sdugks_t *h, const double *rho, const double *u, const dou
 int sdugks_macros(sdugks_t *h, double *rho, double *u, double *v)
 {
     if (!h) return fail(SDUGKS_EINVAL, "null handle");
-    std::vector<double> W(3 * (size_t)h->mb.nc);
-    int rc = sdugks_get_state(h, nullptr, W.data(), nullptr);
-    if (rc) return rc;
-    for (int32_t c = 0; c < h->mb.nc; c++) {
-        if (rho) rho[c] = W[3 * c];
-        if (u) u[c] = W[3 * c + 1] / W[3 * c];
-        if (v) v[c] = W[3 * c + 2] / W[3 * c];
-    }
+    HIPCHK(hipSetDevice(h->device));
+    // through the W rows that the next step writes
+    const size_t nc = h->mb.nc;
+    double *const stage = h->at<double>(h->L.off_W[h->cur ^ 1]);
+    HIPCHK(launch_state_io(kGetMacros, h->io, 0, (int)nc, h->at<double>(h->L.off_W[h->cur]), nullptr, nullptr, stage, h->stream));
+    double *const dst[3] = {rho, u, v};
+    for (int k = 0; k < 3; k++)
+        if (dst[k]) HIPCHK(hipMemcpyAsync(dst[k], stage + k * nc, nc * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
     return SDUGKS_OK;
 }
 

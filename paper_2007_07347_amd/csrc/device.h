@@ -262,6 +262,21 @@ hipError_t launch_reduce_packs(const ReduceJob *jobs, int n, double *out, hipStr
 // rho0 < 0), W, G = 0 and the residual snapshot.
 hipError_t launch_set_equilibrium(int nc, int np, const double *m3, double *f, float *f32, double rho0, double *W,
                                   double *G, double *snap, hipStream_t st);
+// State between the caller's cell order (cell-major arrays, n cells from c0 on)
+// and the internal rows: macros or W, G ([n][3]) or f ([n][9]) out, W, G or f in.
+// kGetF and kPutF need the W that goes with f; kPutRows3 also sets the residual's
+// snapshot where snap is given.
+enum StateMove { kGetMacros, kGetRows3, kPutRows3, kGetF, kPutF };
+struct StateLayout {
+    int32_t np, mode;
+    const int32_t *iperm;               // [nc] internal index of a caller's cell, NULL where the orders agree
+    double rho0, k;                     // k: dt / (2 tau) of the original scheme's variable, else 0
+};
+hipError_t launch_state_io(StateMove move, const StateLayout &l, int c0, int n, const double *W, void *rows, double *snap,
+                           double *host_order, hipStream_t st);
+// The same f (as stored) and W in every cell, G = 0, snapshot = its velocity.
+hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3, double *f, float *f32, double *W,
+                              double *G, double *snap, hipStream_t st);
 // *p = NaN, p pointing at a double (bytes 8) or a float (bytes 4): failure injection.
 hipError_t launch_poke_nan(void *p, int bytes, hipStream_t st);
 

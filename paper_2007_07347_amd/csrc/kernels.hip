@@ -246,6 +246,110 @@ __global__ void __launch_bounds__(256) k_set_equilibrium(int nc, int np, const d
     snap[np + c] = my / r;
 }
 
+// State in and out of the library's layout on the device: n cells of the
+// caller's order from c0 on, against the rows of the internal order (iperm:
+// internal index of a caller's cell; NULL where the two orders are the same).
+// Host loops over the same moved about 1 GB/s, these run at the rate of the copy
+// to or from the host.
+struct StateIO {
+    int c0, n, np;
+    const int32_t *iperm;
+    int mode;                   // storage of f, as for the step
+    double rho0, k;             // k = dt / (2 tau) where the stored variable is ft = (1 + k) f - k feq (original scheme), else 0
+    __device__ int cell(int t) const { return iperm ? iperm[c0 + t] : c0 + t; }
+};
+
+__global__ void __launch_bounds__(256) k_get_macros(StateIO io, const double *W, double *out)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= io.n) return;
+    const int c = io.cell(t);
+    const double r = W[c];
+    out[t] = r;
+    out[(size_t)io.n + t] = W[(size_t)io.np + c] / r;
+    out[2 * (size_t)io.n + t] = W[2 * (size_t)io.np + c] / r;
+}
+
+__global__ void __launch_bounds__(256) k_get_rows3(StateIO io, const double *rows, double *out)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= io.n) return;
+    const int c = io.cell(t);
+    for (int r = 0; r < 3; r++) out[3 * (size_t)t + r] = rows[r * (size_t)io.np + c];
+}
+
+// snap: also the residual's snapshot, the velocity of the W put here
+__global__ void __launch_bounds__(256) k_put_rows3(StateIO io, const double *in, double *rows, double *snap)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= io.n) return;
+    const int c = io.cell(t);
+    double v[3];
+    for (int r = 0; r < 3; r++) rows[r * (size_t)io.np + c] = v[r] = in[3 * (size_t)t + r];
+    if (snap) {
+        snap[c] = v[1] / v[0];
+        snap[(size_t)io.np + c] = v[2] / v[0];
+    }
+}
+
+__global__ void __launch_bounds__(256) k_get_f(StateIO io, const double *W, const void *f, double *out)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= io.n) return;
+    const int c = io.cell(t);
+    const size_t np = io.np;
+    const double r = W[c], ux = W[np + c] / r, uy = W[2 * np + c] / r;
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        const double fe = feq_one(kW[i], kEx[i], kEy[i], r, ux, uy);
+        double x;
+        if (io.mode == SDUGKS_FP64) x = ((const double *)f)[i * np + c];
+        else x = (io.mode == SDUGKS_FP32NEQ ? fe : kW[i] * io.rho0) + (double)((const float *)f)[i * np + c];
+        if (io.k != 0.0) x = (x + io.k * fe) / (1.0 + io.k);
+        out[9 * (size_t)t + i] = x;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_put_f(StateIO io, const double *W, const double *in, void *f)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= io.n) return;
+    const int c = io.cell(t);
+    const size_t np = io.np;
+    const double r = W[c], ux = W[np + c] / r, uy = W[2 * np + c] / r;
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        const double fe = feq_one(kW[i], kEx[i], kEy[i], r, ux, uy);
+        double x = in[9 * (size_t)t + i];
+        if (io.k != 0.0) x = (1.0 + io.k) * x - io.k * fe;
+        if (io.mode == SDUGKS_FP64) ((double *)f)[i * np + c] = x;
+        else ((float *)f)[i * np + c] = (float)(x - (io.mode == SDUGKS_FP32NEQ ? fe : kW[i] * io.rho0));
+    }
+}
+
+// Every cell the same f (as stored), W and velocity; G = 0.
+struct Uniform {
+    double f[9], W[3];
+};
+__global__ void __launch_bounds__(256) k_set_uniform(int nc, int np, Uniform u, double *f, float *f32, double *W, double *G,
+                                                     double *snap)
+{
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= nc) return;
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        if (f32) f32[(size_t)i * np + c] = (float)u.f[i];
+        else f[(size_t)i * np + c] = u.f[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        W[(size_t)i * np + c] = u.W[i];
+        G[(size_t)i * np + c] = 0.0;
+    }
+    snap[c] = u.W[1] / u.W[0];
+    snap[(size_t)np + c] = u.W[2] / u.W[0];
+}
+
 __global__ void k_poke_nan(void *p, int bytes)
 {
     if (bytes == 8) *reinterpret_cast<double *>(p) = __builtin_nan("");
@@ -294,6 +398,31 @@ hipError_t launch_set_equilibrium(int nc, int np, const double *m3, double *f, f
 {
     hipLaunchKernelGGL(k_set_equilibrium, dim3((nc + 255) / 256), dim3(256), 0, st, nc, np, m3, f, f32, rho0, W, G,
                        snap);
+    return hipGetLastError();
+}
+
+hipError_t launch_state_io(StateMove move, const StateLayout &l, int c0, int n, const double *W, void *rows, double *snap,
+                           double *host_order, hipStream_t st)
+{
+    const StateIO io{c0, n, l.np, l.iperm, l.mode, l.rho0, l.k};
+    const dim3 grid((n + 255) / 256), blk(256);
+    switch (move) {
+    case kGetMacros: hipLaunchKernelGGL(k_get_macros, grid, blk, 0, st, io, W, host_order); break;
+    case kGetRows3: hipLaunchKernelGGL(k_get_rows3, grid, blk, 0, st, io, (const double *)rows, host_order); break;
+    case kPutRows3: hipLaunchKernelGGL(k_put_rows3, grid, blk, 0, st, io, host_order, (double *)rows, snap); break;
+    case kGetF: hipLaunchKernelGGL(k_get_f, grid, blk, 0, st, io, W, rows, host_order); break;
+    case kPutF: hipLaunchKernelGGL(k_put_f, grid, blk, 0, st, io, W, host_order, rows); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3, double *f, float *f32, double *W,
+                              double *G, double *snap, hipStream_t st)
+{
+    Uniform u;
+    for (int i = 0; i < 9; i++) u.f[i] = f9[i];
+    for (int i = 0; i < 3; i++) u.W[i] = W3[i];
+    hipLaunchKernelGGL(k_set_uniform, dim3((nc + 255) / 256), dim3(256), 0, st, nc, np, u, f, f32, W, G, snap);
     return hipGetLastError();
 }
 
