@@ -997,12 +997,16 @@ int batch_build_tables(sdugks_batch_t *b)
         }
         g->members.push_back((int)k);
         const int n_bc = (int)h->mb.bcs.size();
-        size_t lds = march_lds_bytes(n_bc);
-        if (form == kGeneral) {
+        size_t lds;
+        if (form == kMarch) {
+            DevCart c = h->dc;
+            cart_cut(c, plan.rows);
+            lds = march_lds_bytes(c, n_bc, mode);
+        } else if (form == kGeneral) {
             g->block = std::max(g->block, h->block);
             g->own_block = g->own_block && h->own_block;
             lds = step_tiled_lds_bytes(h->dt, mode, n_bc);
-        } else if (form != kMarch) {
+        } else {
             g->block = plan.threads;
             lds = step_block_lds_bytes(plan.threads, mode, n_bc);
         }

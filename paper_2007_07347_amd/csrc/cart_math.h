@@ -304,38 +304,49 @@ __device__ __forceinline__ void cell_update(const DevMesh &m, int lagged, double
     rn = fma_(-dtv, G0, ro);
     mxn = fma_(-dtv, G1, mxo);
     myn = fma_(-dtv, G2, myo);
-    const double irn = recip(rn), off = DEV ? m.rho0 : 0.0;
-    double fe[9], feo[9];
-    feq9(rn, mxn, myn, mxn * irn, myn * irn, off, fe);
-    // feq(W^n) where the storage form or the original scheme needs it
-    if (NEQ || m.scheme != 0) {
+    const double irn = recip(rn), un = mxn * irn, vn = myn * irn, off = DEV ? m.rho0 : 0.0;
+    const double inv = m.inv1l, lw[3] = {m.lam * (4.0 / 9), m.lam * (1.0 / 9), m.lam * (1.0 / 36)};
+    double fe[9], feo[9], x[9];
+    // feq(W^n), that the storage form or the original scheme needs
+    auto before = [&]() {
         const double iro = recip(ro);
         feq9(ro, mxo, myo, mxo * iro, myo * iro, off, feo);
-    }
-    const double inv = m.inv1l, lw[3] = {m.lam * (4.0 / 9), m.lam * (1.0 / 9), m.lam * (1.0 / 36)};
-    double x[9];
-    if (m.scheme == 0) {
+    };
+    // the original scheme: ft^{n+1} = (4/3) fbar+ - (1/3) ft - dt/V F
+    auto original = [&](int i, double f0) {
+        const double c = fma_(4.0 / 3.0, fma_(m.a, f0, m.b * (cWt[i] * feo[i])), (-1.0 / 3.0) * f0);
+        return i == 0 ? c : fma_(-dtv, F[i], c);
+    };
+    if constexpr (NEQ) {
+        feq9(rn, mxn, myn, un, vn, off, fe);
+        before();
         static_for<9>([&](auto I) {
             constexpr int i = I;
-            double f0 = (double)fo[i];
-            if constexpr (NEQ) f0 = fma_(cWt[i], feo[i], f0);
-            x[i] = fma_(lw[i == 0 ? 0 : (i < 5 ? 1 : 2)], fe[i], i == 0 ? f0 : fma_(-dtv, F[i], f0)) * inv;
+            const double f0 = fma_(cWt[i], feo[i], (double)fo[i]);
+            x[i] = m.scheme != 0 ? original(i, f0)
+                                 : fma_(lw[i == 0 ? 0 : (i < 5 ? 1 : 2)], fe[i], i == 0 ? f0 : fma_(-dtv, F[i], f0)) * inv;
+            v[i] = (Stored<PM>)fma_(-cWt[i], fe[i], x[i]);
+        });
+    } else if (m.scheme == 0) {
+        // (the equilibria in either branch: held across them they cost the march
+        // the registers of a third wave)
+        static_for<9>([&](auto I) {
+            constexpr int i = I;
+            x[i] = (double)fo[i];
+            if constexpr (i != 0) x[i] = fma_(-dtv, F[i], x[i]);
+        });
+        feq9(rn, mxn, myn, un, vn, off, fe);
+        static_for<9>([&](auto I) {
+            constexpr int i = I;
+            v[i] = (Stored<PM>)(fma_(lw[i == 0 ? 0 : (i < 5 ? 1 : 2)], fe[i], x[i]) * inv);
         });
     } else {
-        // the original scheme: ft^{n+1} = (4/3) fbar+ - (1/3) ft - dt/V F
+        before();
         static_for<9>([&](auto I) {
             constexpr int i = I;
-            double f0 = (double)fo[i];
-            if constexpr (NEQ) f0 = fma_(cWt[i], feo[i], f0);
-            const double c = fma_(4.0 / 3.0, fma_(m.a, f0, m.b * (cWt[i] * feo[i])), (-1.0 / 3.0) * f0);
-            x[i] = i == 0 ? c : fma_(-dtv, F[i], c);
+            v[i] = (Stored<PM>)original(i, (double)fo[i]);
         });
     }
-    static_for<9>([&](auto I) {
-        constexpr int i = I;
-        if constexpr (NEQ) x[i] = fma_(-cWt[i], fe[i], x[i]);
-        v[i] = (Stored<PM>)x[i];
-    });
 }
 
 }  // namespace

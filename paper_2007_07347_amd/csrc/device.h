@@ -216,7 +216,7 @@ inline bool block_wraps(const DevCart &c, const CartBlock &B)
 // which all wrap rows inside a box or all do not.
 hipError_t launch_step_batch_block(const BatchTable &tab, bool wrap, int threads, int mode, int steps, int parity,
                                    int cap_tiles, size_t lds, hipStream_t st, GraphChain *gc = nullptr);
-size_t march_lds_bytes(int n_bc);       // besides the march's static LDS
+size_t march_lds_bytes(const DevCart &c, int n_bc, int mode);   // besides the march's static LDS
 // Workgroups of a structured instance cut into strips and segments.
 inline int32_t cart_groups(const DevCart &c) { return c.strips * c.segs; }
 hipError_t launch_step_batch_cart(const BatchTable &tab, int mode, int parity, int cap_tiles, size_t lds,

@@ -7,10 +7,10 @@
 //
 // One wave takes a strip of up to 60 columns (one lane per column, two halo
 // columns on either side) and marches along a segment of its rows.  A lane
-// keeps what the rows behind it still need in registers and reads its left and
-// right neighbours by wave shifts, so there is no LDS, no barrier and no value
-// computed twice but those of the halo columns and of the two rows before and
-// after the segment.  When row k arrives:
+// keeps what the rows behind it still need in registers (their W and f in the
+// wave's own LDS) and reads its left and right neighbours by wave shifts, so no
+// wave waits for another and no value is computed twice but those of the halo
+// columns and of the two rows before and after the segment.  When row k arrives:
 //
 //   fbar+ of row k = a f + b feq(W) (Eq. fbarplus), after which the loads of
 //     row k + 1 are issued into the same registers;
@@ -28,6 +28,15 @@
 // adjacent cell's slopes, the others the adjacent cell's reconstruction; the
 // boundary state is a least-squares point at the face midpoint.  The lane (or
 // row) outside a wall stands for the boundary state.
+//
+// What bounds it is memory: with the arithmetic left out the same accesses take
+// 29.0 of 33.3 us on 1024 x 1024 cells in FP32 deviations and 43.7 of 47.2 in
+// FP64 (12 values in and out per cell, each array a stream of some 240 bytes per
+// wave and row), and three waves on a SIMD instead of two, requests of two rows
+// ahead, or cache lines touched before they are requested change nothing or cost
+// 5 to 20 %; so do non-temporal stores.  Before it, one workgroup per 16 x 14 or
+// 16 x 7 cells with their halo in LDS: 52.8 and 86.7 us, 1430 lane instructions
+// per cell against 550; now 31.7 and 46.0.
 #include <cstdint>
 #include <type_traits>
 #include <utility>
@@ -127,9 +136,9 @@ struct March {
     const DevState &s;
     const int lagged, j0, j1;
     size_t np;
-    int cc, xtag;
+    int cc;
     int kend, klow, khigh, wrap;        // rows below kend are read; the rows outside the walls (none where periodic)
-    bool out, wall_r, ghost_l, edge;
+    bool out, wall_r, ghost_l, ghost_r, at_l, at_r, edge;
     uint32_t offv, offw;                // byte offsets of this lane's column in a row of f, of W
     const Factors<PM> c;
     R hl, hr, wl, wr, Cy, Cy1, Cy5;
@@ -137,32 +146,36 @@ struct March {
     // requested: W and f of the next row
     double W[3];
     V fv[9];
-    int side;                           // and its boundary entry on the left or right, where the lane is outside
     const WallBC *const bcs;
     // W and f of the last kRing rows, [row % kRing][value][lane]: the wave's own LDS
     double *const lw;
     V *const lf;
+    // fbar+ of the boundary states in the columns outside the walls less the cell's: rows of
+    // the march, nine values each, for the left column and then the right
+    R *const lx;
 
     __device__ __forceinline__ March(const DevMesh &m_, const DevCart &c_, const DevState &s_, int lagged_, int i0,
-                                     int w, int j0_, int j1_, Ring<PM> &ring, const WallBC *bcs_)
+                                     int w, int j0_, int j1_, Ring<PM> &ring, const WallBC *bcs_, R *lx_)
         : m(m_), cg(c_), s(s_), lagged(lagged_), j0(j0_), j1(j1_), c(m_), bcs(bcs_), lw(ring.W[0][0] + (threadIdx.x & 63)),
-          lf(ring.f[0][0] + (threadIdx.x & 63))
+          lf(ring.f[0][0] + (threadIdx.x & 63)), lx(lx_)
     {
         const int nx = cg.nx;
         np = (size_t)m.np;
-        const int lane = (int)(threadIdx.x & 63), ci = i0 - 2 + lane;   // this lane's column, before wrapping
+        const int lane = (int)(threadIdx.x & 63);
+        const int ci = i0 - 2 + (lane < w + 3 ? lane : w + 3);          // this lane's column, before wrapping
         if (cg.per_x) {
             cc = ci < 0 ? ci + nx : (ci >= nx ? ci - nx : ci);
-            if (cc >= nx) cc = 0;       // lanes past the halo of a narrow strip
         } else {
             cc = ci < 0 ? 0 : (ci >= nx ? nx - 1 : ci);
         }
         out = lane >= 2 && lane < w + 2;                // this lane's cells are written
         // the columns outside the walls hold boundary states; whether the strip has one
-        ghost_l = !cg.per_x && ci == -1;
+        at_l = !cg.per_x && i0 <= 1;
+        at_r = !cg.per_x && i0 + w + 1 >= nx;
+        edge = at_l || at_r;
+        ghost_l = at_l && ci == -1;
+        ghost_r = at_r && ci == nx;
         wall_r = !cg.per_x && ci == nx - 1;
-        xtag = ghost_l ? 2 * nx : (!cg.per_x && ci == nx ? 2 * nx + cg.ny : -1);
-        edge = !cg.per_x && (i0 <= 1 || i0 + w + 1 >= nx);
         offv = (uint32_t)cc * (uint32_t)sizeof(V);
         offw = (uint32_t)cc * 8u;
         const gmem<double> *const col = gin(cg.col) + (size_t)cc * kCartVals;
@@ -184,8 +197,6 @@ struct March {
         ld_rows<3>(s.W + g, np, offw, W);
         if constexpr (PM == SDUGKS_FP64) ld_rows<9>(s.f + g, np, offv, fv);
         else ld_rows<9>(s.f32 + g, np, offv, fv);
-        side = -1;
-        if (edge && xtag >= 0) side = gin(cg.side)[xtag + row];
     }
     // Wait for the requested row here, before the update's stores are issued:
     // the counter of outstanding accesses is in order, so a wait at the next
@@ -197,22 +208,40 @@ struct March {
         for (int i = 0; i < 3; i++) asm volatile("" : "+v"(W[i]));
 #pragma unroll
         for (int i = 0; i < 9; i++) asm volatile("" : "+v"(fv[i]));
-        asm volatile("" : "+v"(side));
 #endif
     }
-    // fbar+ of row k, requested before
+    // The boundary states' part in the columns outside the walls, one lane per row from row k on:
+    // in the march it took every lane of the strip a fifth of the row's time.
+    __device__ __forceinline__ void columns(int k, int rows) const
+    {
+        for (int n = (int)(threadIdx.x & 63); n < rows; n += 64) {
+            int j = k + n;
+            if (cg.per_y) j = j < 0 ? j + cg.ny : j % cg.ny;
+            else j = j < 0 ? 0 : (j >= cg.ny ? cg.ny - 1 : j);
+            const gmem<double> *const Wj = gin(s.W) + at(j);
+            auto column = [&](int i, int tags, R *to) {
+                R df[9];
+                wall_diff<PM>(m, bcs[gin(cg.side)[tags + j]], Wj[i], Wj[np + i], Wj[2 * np + i], df);
+#pragma unroll
+                for (int e = 0; e < 9; e++) to[n * 9 + e] = df[e];
+            };
+            if (at_l) column(0, 2 * cg.nx, lx);
+            if (at_r) column(cg.nx - 1, 2 * cg.nx + cg.ny, lx + (at_l ? rows * 9 : 0));
+        }
+    }
+    // fbar+ of row k, requested before; the cells outside the walls read the cell inside and hold the boundary state
     __device__ __forceinline__ void arrive(int k, R fb[9]) const
     {
-        const bool beyond = k == klow || k == khigh;
-        int tag = side;
-        if (beyond) tag = gin(cg.side)[(k == klow ? 0 : cg.nx) + cc];
         cell_plus<PM>(m, c, W[0], W[1], W[2], fv, fb);
-        if (edge || beyond) {
-            // columns and rows outside a wall read the cell inside it and hold the boundary state
+        if (k == klow || k == khigh) {
+            const int tag = gin(cg.side)[(k == klow ? 0 : cg.nx) + cc];
             R df[9];
-            wall_diff<PM>(m, bcs[tag < 0 ? 0 : tag], W[0], W[1], W[2], df);
+            wall_diff<PM>(m, bcs[tag], W[0], W[1], W[2], df);
 #pragma unroll
-            for (int i = 0; i < 9; i++) fb[i] = tag < 0 ? fb[i] : fb[i] + df[i];
+            for (int i = 0; i < 9; i++) fb[i] += df[i];
+        } else if (edge && (ghost_l || ghost_r)) {
+#pragma unroll
+            for (int i = 0; i < 9; i++) fb[i] += wx[i];
         }
     }
     // W and f of the row in ring slot t, put there when it arrived
@@ -231,31 +260,14 @@ struct March {
         for (int i = 0; i < 9; i++) fo[i] = lf[(t * 9 + i) * 64];
     }
 
-    __device__ __forceinline__ void update(int row, double irow, const Outflow &o, const double Wp[3], const V fo[9])
-    {
-        const size_t g = at(row);
-        const double dtv = icol * irow;
-        double G[3] = {0.0, 0.0, 0.0}, Wn[3];
-        if (lagged) ld_rows<3>(s.G + g, np, offw, G);
-        V v[9];
-        cell_update<PM>(m, lagged, dtv, Wp[0], Wp[1], Wp[2], o, fo, G, Wn[0], Wn[1], Wn[2], v);
-        settle();
-        if (out) {
-            st_rows<3>(s.Wo + g, np, offw, Wn);
-            if constexpr (PM == SDUGKS_FP64) st_rows<9>(s.fo + g, np, offv, v);
-            else st_rows<9>(s.fo32 + g, np, offv, v);
-            if (lagged) st_rows<3>(s.Go + g, np, offw, G);
-        }
-    }
-
     // State of the march between rows.
-    R fbp[9], gyp[9];                   // of row k - 1: fbar+, and the lower term of its slope along y
-    R dlow[3];                          // and its differences to row k - 2 of the velocities entering from below
+    R fbp[9], dyp[9];                   // of row k - 1: fbar+, and its differences to row k - 2
     Side<R> top;                        // of row k - 2: its upper side,
-    Outflow acc;                        // the outflow through its other faces
+    R px[3], nx[3], py[3], ny[3];       // the fluxes through its upper x face and its lower y face
     double ip;                          // and 1 / height
     CartRow<R> rq;                      // record of row k - 1
     int t, row;                         // ring slot of row k, its index (wrapped, or inside the wall)
+    const R *wx;                        // the part above of row k in this lane's column, where it is outside
 
     // Row k arrives.
     template <bool UPDATE>
@@ -272,14 +284,14 @@ struct March {
         for (int i = 0; i < 9; i++) dy[i] = fb[i] - fbp[i];
         const bool wall_t = q == khigh - 1;
         if (UPDATE || (q >= j0 - 1 && q > klow)) {
-            const R hb = uniform(rq.hb), ht = uniform(rq.ht), wt = uniform(rq.wt), Cx = uniform(rq.c);
+            const R hb = uniform(rq.hb), ht = uniform(rq.ht), wb = uniform(rq.wb), wt = uniform(rq.wt), Cx = uniform(rq.c);
             R gx[9], gy[9], bk[9], dr[3], dl[3];
 #pragma unroll
             for (int i = 0; i < 9; i++) {
                 const R dp = shift<kNext>(fbp[i]) - fbp[i];
                 const R dm = shift<kPrev>(dp);
                 gx[i] = slope(wl, wr, dm, dp);
-                gy[i] = fma_(wt, dy[i], gyp[i]);
+                gy[i] = slope(wb, wt, dyp[i], dy[i]);
                 // of the velocities entering on the left and on the right
                 for (int e = 0; e < 3; e++) {
                     if (i == cP[0][e]) dl[e] = dm;
@@ -293,37 +305,32 @@ struct March {
                 // the x faces (of no use for the row after the segment)
                 Side<R> left, right;
                 sides<0>(hl, hr, bk, gx, left, right);
-                Side<R> nx = shift<kNext>(left);
+                Side<R> beside = shift<kNext>(left);
                 if (edge) {
 #pragma unroll
                     for (int e = 0; e < 3; e++) {
                         const R v = shift<kNext>(bk[cP[0][e]] - dl[e]);
                         right.c[e] = ghost_l ? v : right.c[e];
-                        nx.c[e] = wall_r ? bk[cN[0][e]] + dr[e] : nx.c[e];
+                        beside.c[e] = wall_r ? bk[cN[0][e]] + dr[e] : beside.c[e];
                     }
-                    right.s = ghost_l ? nx.s : right.s;
-                    right.d = ghost_l ? nx.d : right.d;
-                    nx.s = wall_r ? right.s : nx.s;
-                    nx.d = wall_r ? right.d : nx.d;
+                    right.s = ghost_l ? beside.s : right.s;
+                    right.d = ghost_l ? beside.d : right.d;
+                    beside.s = wall_r ? right.s : beside.s;
+                    beside.d = wall_r ? right.d : beside.d;
                 }
-                R pr[3], nr[3], pl[3], nl[3];
-                face_flux<PM>(m, right, nx, Cx, Cx * c.k1, Cx * c.k5, pr, nr);
-#pragma unroll
-                for (int e = 0; e < 3; e++) { pl[e] = shift<kPrev>(pr[e]); nl[e] = shift<kPrev>(nr[e]); }
+                R pr[3], nr[3];
+                face_flux<PM>(m, right, beside, Cx, Cx * c.k1, Cx * c.k5, pr, nr);
                 if (!UPDATE && q == klow + 1) {
 #pragma unroll
-                    for (int e = 0; e < 3; e++) top.c[e] = bk[cP[1][e]] - dlow[e];
+                    for (int e = 0; e < 3; e++) top.c[e] = bk[cP[1][e]] - dyp[cP[1][e]];
                     top.s = lower.s;
                     top.d = lower.d;
                 }
                 R p[3], n[3];
                 face_flux<PM>(m, top, lower, Cy, Cy1, Cy5, p, n);
-                if constexpr (UPDATE) {
-                    outflow_above(acc, p, n);
-                    update(q - 1);
-                }
-                outflow_x<0>(acc, pr, nr, pl, nl);
-                outflow_below(acc, p, n);
+                if constexpr (UPDATE) update(q - 1, p, n);
+#pragma unroll
+                for (int e = 0; e < 3; e++) { px[e] = pr[e]; nx[e] = nr[e]; py[e] = p[e]; ny[e] = n[e]; }
             }
             top = upper;
             if (wall_t) {
@@ -333,26 +340,36 @@ struct March {
             }
         }
         if constexpr (!UPDATE) settle();
-        const R wb = uniform(rk.wb);
 #pragma unroll
-        for (int i = 0; i < 9; i++) { fbp[i] = fb[i]; gyp[i] = (-wb) * dy[i]; }
-        if constexpr (!UPDATE) {
-#pragma unroll
-            for (int e = 0; e < 3; e++) dlow[e] = dy[cP[1][e]];
-        }
+        for (int i = 0; i < 9; i++) { fbp[i] = fb[i]; dyp[i] = dy[i]; }
         ip = rq.ih;
+        wx += 9;
         rq = rk;
         row = next;
     }
 
-    __device__ __forceinline__ void update(int p)
+    // Row j, pu and nu the fluxes through its upper face.
+    __device__ __forceinline__ void update(int j, const R pu[3], const R nu[3])
     {
-        const size_t g = at(p);
+        const size_t g = at(j);
+        R pl[3], nl[3];
+#pragma unroll
+        for (int e = 0; e < 3; e++) { pl[e] = shift<kPrev>(px[e]); nl[e] = shift<kPrev>(nx[e]); }
+        Outflow acc;
+        outflow_x<0>(acc, px, nx, pl, nl);
+        outflow_below(acc, py, ny);
+        outflow_above(acc, pu, nu);
         const double dtv = icol * ip;
         double Wp[3], G[3] = {0.0, 0.0, 0.0}, Wn[3];
         V fo[9], v[9];
         kept(t, Wp, fo);
-        if (lagged) ld_rows<3>(s.G + g, np, offw, G);
+        if (lagged) {
+            ld_rows<3>(s.G + g, np, offw, G);
+#if defined(__HIP_DEVICE_COMPILE__)
+            // waited for here, or all that was requested is waited for in either mode
+            asm volatile("" : "+v"(G[0]), "+v"(G[1]), "+v"(G[2]));
+#endif
+        }
         cell_update<PM>(m, lagged, dtv, Wp[0], Wp[1], Wp[2], acc, fo, G, Wn[0], Wn[1], Wn[2], v);
         settle();
         if (out) {
@@ -365,32 +382,34 @@ struct March {
 
     __device__ __forceinline__ void run()
     {
-        const int ny = cg.ny;
+        const int rows = cg.ny;
         const bool per_y = cg.per_y != 0;
         klow = per_y ? INT32_MIN / 2 : -1;
-        khigh = per_y ? INT32_MAX : ny;
-        wrap = per_y ? 0 : ny - 1;
+        khigh = per_y ? INT32_MAX : rows;
+        wrap = per_y ? 0 : rows - 1;
         int k = per_y || j0 >= 1 ? j0 - 2 : -1;
-        kend = per_y || j1 + 1 <= ny ? j1 + 2 : ny + 1;
-        row = k < 0 ? (per_y ? k + ny : 0) : k;
-        if (k + 1 == 0 && k != klow) row = ny - 1;
+        kend = per_y || j1 + 1 <= rows ? j1 + 2 : rows + 1;
+        row = k < 0 ? (per_y ? k + rows : 0) : k;
+        if (k + 1 == 0 && k != klow) row = rows - 1;
         t = 0;
 #pragma unroll
-        for (int i = 0; i < 9; i++) { fbp[i] = 0; gyp[i] = 0; }
+        for (int i = 0; i < 9; i++) { fbp[i] = 0; dyp[i] = 0; }
         top = {};
-        acc = {};
+        for (int e = 0; e < 3; e++) px[e] = nx[e] = py[e] = ny[e] = 0;
         request(row);
+        wx = lx + (at_l && ghost_r ? (kend - k) * 9 : 0);
+        if (edge) columns(k, kend - k);
+        __syncthreads();
         rq = record(row);
         for (; k <= j0 + 1; k++) step<false>(k);
         for (; k < kend; k++) step<true>(k);
-        if (!per_y && j1 == ny) {
+        if (!per_y && j1 == rows) {
             // the face between the last row and the upper wall
             const Side<R> in{{fbp[0], fbp[1], fbp[2]}, top.s, top.d};
             R p[3], n[3];
             face_flux<PM>(m, top, in, Cy, Cy1, Cy5, p, n);
-            outflow_above(acc, p, n);
             t = t == kRing - 1 ? 0 : t + 1;
-            update(ny - 1);
+            update(rows - 1, p, n);
         }
     }
 };
@@ -400,7 +419,8 @@ struct March {
 template <int PM>
 __device__ __forceinline__ void march_unit(const DevMesh &m, const DevCart &cg, const DevState &s, int lagged, int u)
 {
-    extern __shared__ WallBC bcs[];      // [n_bc]
+    // [n_bc] boundary entries, then the columns outside the walls
+    extern __shared__ WallBC bcs[];
     static_assert(kMaxTileBcs <= 64, "one thread per boundary entry");
     if ((int)threadIdx.x < m.n_bc) {
         const DevBC b = gin(m.bcs)[threadIdx.x];
@@ -413,8 +433,9 @@ __device__ __forceinline__ void march_unit(const DevMesh &m, const DevCart &cg, 
     const int i0 = strip * cg.strip_w + (strip < cg.strip_more ? strip : cg.strip_more);
     const int j0 = seg * cg.seg_h + (seg < cg.seg_more ? seg : cg.seg_more);
     __shared__ Ring<PM> ring;
-    March<PM>(m, cg, s, lagged, i0, cg.strip_w + (strip < cg.strip_more), j0, j0 + cg.seg_h + (seg < cg.seg_more), ring,
-              bcs).run();
+    const int w = strip + 1 < cg.strips ? cg.strip_w + (strip < cg.strip_more) : cg.nx - i0;
+    March<PM>(m, cg, s, lagged, i0, w, j0, j0 + cg.seg_h + (seg < cg.seg_more), ring, bcs,
+              (Arith<PM> *)(bcs + m.n_bc)).run();
 }
 
 // The units of an instance, one per workgroup (so that the dispatcher evens
@@ -447,13 +468,19 @@ __global__ void __launch_bounds__(64, 2) k_step_batch_cart(BatchTable tab, int p
 
 }  // namespace
 
-size_t march_lds_bytes(int n_bc) { return n_bc * sizeof(WallBC); }
+// Boundary entries, and nine values for each row of a segment and the two on either side of it,
+// for both columns outside the walls where one strip holds both.
+size_t march_lds_bytes(const DevCart &c, int n_bc, int mode)
+{
+    const size_t rows = c.seg_h + (c.seg_more > 0) + 4, value = mode == SDUGKS_FP32DEV ? sizeof(float) : sizeof(double);
+    return n_bc * sizeof(WallBC) + (c.per_x ? 0 : (c.strips == 1 ? 2 : 1) * rows * 9 * value);
+}
 
 hipError_t launch_step_cart(const DevMesh &m, const DevCart &c, const DevState &s, int lagged, int mode,
                             hipStream_t st, GraphChain *gc)
 {
     const dim3 grid((unsigned)cart_groups(c)), blk(64);
-    const size_t lds = march_lds_bytes(m.n_bc);
+    const size_t lds = march_lds_bytes(c, m.n_bc, mode);
     if (mode == SDUGKS_FP32DEV) return emit(&k_step_cart<SDUGKS_FP32DEV>, grid, blk, lds, st, gc, m, c, s, lagged);
     if (mode == SDUGKS_FP32NEQ) return emit(&k_step_cart<SDUGKS_FP32NEQ>, grid, blk, lds, st, gc, m, c, s, lagged);
     return emit(&k_step_cart<SDUGKS_FP64>, grid, blk, lds, st, gc, m, c, s, lagged);

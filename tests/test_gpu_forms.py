@@ -1,7 +1,7 @@
 """The two forms of the structured step -- waves marching along strips, and
 boxes that take several steps per launch -- at the sizes where their cuts can
 go wrong: meshes that just fit a box or are one cell too large, halves and
-remainders of strips (60 columns) and boxes (16 and 32 cells), periodic meshes
+remainders of strips (60 columns, or multiples of eight) and boxes (16 and 32 cells), periodic meshes
 narrower than a box (rows that wrap inside it) and wider ones, two cells along
 an axis.  Small meshes alone take boxes; in one batch with a 640 x 640 cavity
 they take the march; one launch per step (step_eager) takes boxes of one step.
@@ -48,11 +48,11 @@ def _rect(nx, ny):
 
 SHAPES = {
     "walls": (_rect, [(2, 2), (2, 9), (9, 2), (14, 16), (14, 32), (15, 33), (30, 16), (31, 17), (60, 5), (61, 60), (62, 8),
-                      (63, 24), (120, 31), (121, 64), (181, 90)]),
-    "periodic": (meshgen.periodic_box, [(2, 2), (4, 64), (5, 65), (16, 32), (17, 33), (64, 8), (65, 9), (61, 120)]),
+                      (63, 24), (104, 17), (112, 9), (120, 31), (121, 64), (168, 33), (181, 90)]),
+    "periodic": (meshgen.periodic_box, [(2, 2), (4, 64), (5, 65), (16, 32), (17, 33), (64, 8), (65, 9), (61, 120), (104, 9)]),
     "periodic_x": (meshgen.couette, [(2, 3), (4, 32), (4, 128), (4, 129), (17, 8), (65, 20)]),
     "periodic_y": (_walls_x, [(2, 2), (9, 20), (30, 16), (61, 32)]),
-    "open": (_half_channel, [(13, 7), (31, 15), (62, 40)]),
+    "open": (_half_channel, [(13, 7), (31, 15), (62, 40), (104, 18)]),
 }
 CASES = [(kind, n) for kind, (_, sizes) in SHAPES.items() for n in sizes]
 
