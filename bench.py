@@ -53,8 +53,8 @@ _CSRC = os.path.join(ROOT, "paper_2007_07347_amd", "csrc")
 # the sources each step kernel is compiled from (its own file and the shared
 # device helpers): the traffic counters of a kernel hold while these are unchanged
 KERNEL_SOURCES = {
-    "k_step_tiled": ("step_tiled.hip", "step_common.h"),
-    "k_step_batch": ("step_tiled.hip", "step_common.h"),
+    "k_step_tiled": ("step_tiled.hip", "cart_math.h", "step_common.h"),
+    "k_step_batch": ("step_tiled.hip", "cart_math.h", "step_common.h"),
     "k_step_cart": ("step_cart.hip", "cart_math.h", "step_common.h"),
     "k_step_batch_cart": ("step_cart.hip", "cart_math.h", "step_common.h"),
     "k_step_block": ("step_block.hip", "cart_math.h", "step_common.h"),

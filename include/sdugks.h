@@ -70,9 +70,8 @@ enum { SDUGKS_BC_WALL = 1, SDUGKS_BC_INLET = 2, SDUGKS_BC_OUTLET = 3, SDUGKS_BC_
 
 /* Precision of f.  FP64: stored and computed in FP64.  FP32DEV: stored in
  * FP32 as the deviation f - w_i rho0 and advected in FP32 (fbar+, gradients,
- * face values and fluxes; per-cell flux sums compensated in the general
- * step, in FP64 in the structured step), with density,
- * momentum, their update, the macroscopic flux, mass and residual in FP64;
+ * face values and fluxes), with the per-cell flux sums, density, momentum,
+ * their update, the macroscopic flux, mass and residual in FP64;
  * the rounding of its FP32 arithmetic (fbar+, gradients and face pass
  * alike) keeps the velocity residual from falling below a few 1e-8 on fine
  * meshes.  FP32NEQ: the non-equilibrium
@@ -128,7 +127,8 @@ typedef struct {
                                      (0 = library default, -1 = two-kernel step without tiles; meshes with
                                      polygons of more than four faces or more than 64 boundary-condition
                                      entries always take the two-kernel step) */
-    int32_t block_threads;        /* threads per workgroup of the fused step: 64, 128 or 256 (0 = default) */
+    int32_t block_threads;        /* threads per workgroup of the fused step: 64, 128 or 256 (0 = the library's
+                                     choice: 256 while all tiles are on the chip at once, else 128) */
     int32_t scheme;               /* SDUGKS_SCHEME_SIMPLIFIED (default) or SDUGKS_SCHEME_ORIGINAL */
     int32_t structured;           /* structured step for tensor-product quad meshes (the cells are the
                                      rectangles of two coordinate arrays; periodic sides glued row to row
