@@ -193,15 +193,14 @@ inline bool step_tiled_two(const DevTiles &t, int block) { return t.nl_max > blo
 // Threads of the fused step where the caller leaves them to the library: four
 // waves a tile while all tiles are on the chip at once (three per CU in FP64:
 // a 45,000-cell mesh takes 8.0 us a step, with two waves 8.3), two beyond (a
-// 200,000-cell mesh with FP32 deviations takes 14.3 us, with four waves 17.1).
+// 200,000-cell mesh with FP32 deviations takes 13.4 us, with four waves 17.1).
 inline int step_tiled_block(const DevTiles &t, int64_t n_tiles)
 {
     return n_tiles <= 768 && !step_tiled_two(t, 256) ? 256 : 128;
 }
-// Structured step over the tiles of a tensor-product quad mesh (one
-// workgroup per tile: 16 x 14 cells on 512 threads for FP32 deviations, 16 x 7
-// on 256 threads otherwise), and its batched form (members of one mode on the
-// structured step).
+// Structured step of a tensor-product quad mesh, marching form (a wave per
+// segment of a strip of columns), and below its batched form (members of one
+// mode).
 hipError_t launch_step_cart(const DevMesh &m, const DevCart &c, const DevState &s, int lagged, int mode,
                             hipStream_t st, GraphChain *gc = nullptr);
 // The same, `steps` steps at once (at most B.K unless one box holds the mesh).

@@ -36,7 +36,7 @@
 // ahead, or cache lines touched before they are requested change nothing or cost
 // 5 to 20 %; so do non-temporal stores.  Before it, one workgroup per 16 x 14 or
 // 16 x 7 cells with their halo in LDS: 52.8 and 86.7 us, 1430 lane instructions
-// per cell against 550; now 31.7 and 46.0.
+// per cell against 550; now 30.9 and 44.4.
 #include <cstdint>
 #include <type_traits>
 #include <utility>
@@ -125,8 +125,13 @@ struct Ring {
     Stored<PM> f[kRing][9][64];
 };
 
-// One time step of rows [j0, j1) of the columns [i0, i0 + w), w <= 60, by one wave.
-template <int PM>
+// One time step of rows [j0, j1) of the columns [i0, i0 + w), w <= 60, by one
+// wave, from the lowest row up or (DOWN) from the highest down.  Where
+// neighbouring segments march in opposite directions, both come to the rows they
+// share at the same time and the second finds them in L2 (1024 x 1024 cells, FP32
+// deviations: 86 MB read per step against 115, 63 being the state).  Marching
+// down, march row k is mesh row j0 + j1 - 1 - k; the code below follows march rows.
+template <int PM, bool DOWN>
 struct March {
     using R = Arith<PM>;
     using V = Stored<PM>;
@@ -137,7 +142,7 @@ struct March {
     const int lagged, j0, j1;
     size_t np;
     int cc;
-    int kend, klow, khigh, wrap;        // rows below kend are read; the rows outside the walls (none where periodic)
+    int kend, klow, khigh;              // march rows below kend are read; those outside the walls (far away where periodic)
     bool out, wall_r, ghost_l, ghost_r, at_l, at_r, edge;
     uint32_t offv, offw;                // byte offsets of this lane's column in a row of f, of W
     const Factors<PM> c;
@@ -190,6 +195,13 @@ struct March {
     }
 
     __device__ __forceinline__ size_t at(int row) const { return (size_t)(uint32_t)row * (uint32_t)cg.nx; }
+    // mesh row of march row k: wrapped where periodic, else that inside the wall
+    __device__ __forceinline__ int mesh_row(int k) const
+    {
+        const int j = DOWN ? j0 + j1 - 1 - k : k;
+        if (cg.per_y) return j < 0 ? j + cg.ny : (j >= cg.ny ? j - cg.ny : j);
+        return j < 0 ? 0 : (j >= cg.ny ? cg.ny - 1 : j);
+    }
     __device__ __forceinline__ CartRow<R> record(int row) const { return ld_uniform((const CartRow<R> *)cg.row + row); }
     __device__ __forceinline__ void request(int row)
     {
@@ -215,7 +227,7 @@ struct March {
     __device__ __forceinline__ void columns(int k, int rows) const
     {
         for (int n = (int)(threadIdx.x & 63); n < rows; n += 64) {
-            int j = k + n;
+            int j = DOWN ? j0 + j1 - 1 - (k + n) : k + n;
             if (cg.per_y) j = j < 0 ? j + cg.ny : j % cg.ny;
             else j = j < 0 ? 0 : (j >= cg.ny ? cg.ny - 1 : j);
             const gmem<double> *const Wj = gin(s.W) + at(j);
@@ -234,7 +246,7 @@ struct March {
     {
         cell_plus<PM>(m, c, W[0], W[1], W[2], fv, fb);
         if (k == klow || k == khigh) {
-            const int tag = gin(cg.side)[(k == klow ? 0 : cg.nx) + cc];
+            const int tag = gin(cg.side)[((k == klow) != DOWN ? 0 : cg.nx) + cc];
             R df[9];
             wall_diff<PM>(m, bcs[tag], W[0], W[1], W[2], df);
 #pragma unroll
@@ -262,8 +274,8 @@ struct March {
 
     // State of the march between rows.
     R fbp[9], dyp[9];                   // of row k - 1: fbar+, and its differences to row k - 2
-    Side<R> top;                        // of row k - 2: its upper side,
-    R px[3], nx[3], py[3], ny[3];       // the fluxes through its upper x face and its lower y face
+    Side<R> top;                        // of row k - 2: its side towards row k - 1,
+    R px[3], nx[3], py[3], ny[3];       // the fluxes through its upper x face and the y face to row k - 3
     double ip;                          // and 1 / height
     CartRow<R> rq;                      // record of row k - 1
     int t, row;                         // ring slot of row k, its index (wrapped, or inside the wall)
@@ -273,7 +285,7 @@ struct March {
     template <bool UPDATE>
     __device__ __forceinline__ void step(int k)
     {
-        const int q = k - 1, next = row + 1 == cg.ny ? wrap : (k == klow ? 0 : row + 1);
+        const int q = k - 1, next = mesh_row(k + 1);
         const CartRow<R> rk = record(row);
         R fb[9], dy[9];
         arrive(k, fb);
@@ -281,7 +293,7 @@ struct March {
         t = t == kRing - 1 ? 0 : t + 1;     // now of rows k + 1 and k - 2
         if (k + 1 < kend) request(next);
 #pragma unroll
-        for (int i = 0; i < 9; i++) dy[i] = fb[i] - fbp[i];
+        for (int i = 0; i < 9; i++) dy[i] = DOWN ? fbp[i] - fb[i] : fb[i] - fbp[i];
         const bool wall_t = q == khigh - 1;
         if (UPDATE || (q >= j0 - 1 && q > klow)) {
             const R hb = uniform(rq.hb), ht = uniform(rq.ht), wb = uniform(rq.wb), wt = uniform(rq.wt), Cx = uniform(rq.c);
@@ -291,7 +303,7 @@ struct March {
                 const R dp = shift<kNext>(fbp[i]) - fbp[i];
                 const R dm = shift<kPrev>(dp);
                 gx[i] = slope(wl, wr, dm, dp);
-                gy[i] = slope(wb, wt, dyp[i], dy[i]);
+                gy[i] = DOWN ? slope(wb, wt, dy[i], dyp[i]) : slope(wb, wt, dyp[i], dy[i]);
                 // of the velocities entering on the left and on the right
                 for (int e = 0; e < 3; e++) {
                     if (i == cP[0][e]) dl[e] = dm;
@@ -322,20 +334,23 @@ struct March {
                 face_flux<PM>(m, right, beside, Cx, Cx * c.k1, Cx * c.k5, pr, nr);
                 if (!UPDATE && q == klow + 1) {
 #pragma unroll
-                    for (int e = 0; e < 3; e++) top.c[e] = bk[cP[1][e]] - dyp[cP[1][e]];
-                    top.s = lower.s;
-                    top.d = lower.d;
+                    for (int e = 0; e < 3; e++) top.c[e] = DOWN ? bk[cN[1][e]] + dyp[cN[1][e]] : bk[cP[1][e]] - dyp[cP[1][e]];
+                    top.s = DOWN ? upper.s : lower.s;
+                    top.d = DOWN ? upper.d : lower.d;
                 }
                 R p[3], n[3];
-                face_flux<PM>(m, top, lower, Cy, Cy1, Cy5, p, n);
+                if constexpr (DOWN) face_flux<PM>(m, upper, top, Cy, Cy1, Cy5, p, n);
+                else face_flux<PM>(m, top, lower, Cy, Cy1, Cy5, p, n);
                 if constexpr (UPDATE) update(q - 1, p, n);
 #pragma unroll
                 for (int e = 0; e < 3; e++) { px[e] = pr[e]; nx[e] = nr[e]; py[e] = p[e]; ny[e] = n[e]; }
             }
-            top = upper;
+            top = DOWN ? lower : upper;
             if (wall_t) {
-                // the row above the upper wall ends the march: its side
-                const R in[3] = {bk[cN[1][0]] + dy[cN[1][0]], bk[cN[1][1]] + dy[cN[1][1]], bk[cN[1][2]] + dy[cN[1][2]]};
+                // the row outside the wall ends the march: its side
+                R in[3];
+#pragma unroll
+                for (int e = 0; e < 3; e++) in[e] = DOWN ? bk[cP[1][e]] - dy[cP[1][e]] : bk[cN[1][e]] + dy[cN[1][e]];
                 fb[0] = in[0]; fb[1] = in[1]; fb[2] = in[2];
             }
         }
@@ -348,17 +363,17 @@ struct March {
         row = next;
     }
 
-    // Row j, pu and nu the fluxes through its upper face.
+    // March row j, pu and nu the fluxes through the face to the next.
     __device__ __forceinline__ void update(int j, const R pu[3], const R nu[3])
     {
-        const size_t g = at(j);
+        const size_t g = at(DOWN ? j0 + j1 - 1 - j : j);
         R pl[3], nl[3];
 #pragma unroll
         for (int e = 0; e < 3; e++) { pl[e] = shift<kPrev>(px[e]); nl[e] = shift<kPrev>(nx[e]); }
         Outflow acc;
         outflow_x<0>(acc, px, nx, pl, nl);
-        outflow_below(acc, py, ny);
-        outflow_above(acc, pu, nu);
+        outflow_below(acc, DOWN ? pu : py, DOWN ? nu : ny);
+        outflow_above(acc, DOWN ? py : pu, DOWN ? ny : nu);
         const double dtv = icol * ip;
         double Wp[3], G[3] = {0.0, 0.0, 0.0}, Wn[3];
         V fo[9], v[9];
@@ -382,15 +397,12 @@ struct March {
 
     __device__ __forceinline__ void run()
     {
-        const int rows = cg.ny;
         const bool per_y = cg.per_y != 0;
-        klow = per_y ? INT32_MIN / 2 : -1;
-        khigh = per_y ? INT32_MAX : rows;
-        wrap = per_y ? 0 : rows - 1;
-        int k = per_y || j0 >= 1 ? j0 - 2 : -1;
-        kend = per_y || j1 + 1 <= rows ? j1 + 2 : rows + 1;
-        row = k < 0 ? (per_y ? k + rows : 0) : k;
-        if (k + 1 == 0 && k != klow) row = rows - 1;
+        klow = per_y ? INT32_MIN / 2 : (DOWN ? j0 + j1 - 1 - cg.ny : -1);
+        khigh = per_y ? INT32_MAX / 2 : (DOWN ? j0 + j1 : cg.ny);
+        int k = j0 - 2 > klow ? j0 - 2 : klow;
+        kend = j1 + 2 < khigh + 1 ? j1 + 2 : khigh + 1;
+        row = mesh_row(k);
         t = 0;
 #pragma unroll
         for (int i = 0; i < 9; i++) { fbp[i] = 0; dyp[i] = 0; }
@@ -403,13 +415,14 @@ struct March {
         rq = record(row);
         for (; k <= j0 + 1; k++) step<false>(k);
         for (; k < kend; k++) step<true>(k);
-        if (!per_y && j1 == rows) {
-            // the face between the last row and the upper wall
+        if (khigh == j1) {
+            // the face between the last row and the wall
             const Side<R> in{{fbp[0], fbp[1], fbp[2]}, top.s, top.d};
             R p[3], n[3];
-            face_flux<PM>(m, top, in, Cy, Cy1, Cy5, p, n);
+            if constexpr (DOWN) face_flux<PM>(m, in, top, Cy, Cy1, Cy5, p, n);
+            else face_flux<PM>(m, top, in, Cy, Cy1, Cy5, p, n);
             t = t == kRing - 1 ? 0 : t + 1;
-            update(rows - 1, p, n);
+            update(j1 - 1, p, n);
         }
     }
 };
@@ -434,8 +447,16 @@ __device__ __forceinline__ void march_unit(const DevMesh &m, const DevCart &cg, 
     const int j0 = seg * cg.seg_h + (seg < cg.seg_more ? seg : cg.seg_more);
     __shared__ Ring<PM> ring;
     const int w = strip + 1 < cg.strips ? cg.strip_w + (strip < cg.strip_more) : cg.nx - i0;
-    March<PM>(m, cg, s, lagged, i0, w, j0, j0 + cg.seg_h + (seg < cg.seg_more), ring, bcs,
-              (Arith<PM> *)(bcs + m.n_bc)).run();
+    const int j1 = j0 + cg.seg_h + (seg < cg.seg_more);
+    Arith<PM> *const lx = (Arith<PM> *)(bcs + m.n_bc);
+    // Every other segment downwards on meshes whose state the memory-side cache
+    // holds: 1024 x 1024 cells 31.9 -> 30.9 us (FP32 deviations), 46.3 -> 44.4
+    // (FP64); upwards all on larger ones (2048 x 2048: 128.4 against 129.8, FP64
+    // 253 either way) and in FP32NEQ (39.6 against 40.0).
+    if (PM != SDUGKS_FP32NEQ && (seg & 1) && m.nc < (1 << 21))
+        March<PM, true>(m, cg, s, lagged, i0, w, j0, j1, ring, bcs, lx).run();
+    else
+        March<PM, false>(m, cg, s, lagged, i0, w, j0, j1, ring, bcs, lx).run();
 }
 
 // The units of an instance, one per workgroup (so that the dispatcher evens
