@@ -424,7 +424,6 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
     }
     h->stream = (hipStream_t)stream;
     h->block = prm->block_threads;
-    h->own_block = h->block == 0;
     h->precision = prm->precision;
     h->macro = prm->macro_flux;
     h->scheme = prm->scheme;
@@ -582,6 +581,9 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         h->dt.na_max = mb.na_max;
         h->dt.nt_max = mb.nt_max;
         h->dt.nf_max = std::max<int32_t>(1, mb.nf_max);
+        // 256 is a bound rather than a wish: many tiles of 64 quads take 643 us a step with one
+        // item per thread (2048 x 2048 cells, FP64) and 463 on half the threads
+        h->own_block = h->block == 0 || (h->block == 256 && step_tiled_fits(h->dt, 128));
         if (h->own_block) h->block = step_tiled_block(h->dt, mb.n_tiles);
         h->dt.hdr = h->at<int32_t>(L.off_thdr);
         h->dt.lgid = h->at<int32_t>(L.off_lgid);

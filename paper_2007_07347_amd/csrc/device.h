@@ -190,6 +190,10 @@ size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc);
 // More local cells or faces than threads (never more than twice as many, nor
 // more cells of tile and first ring than threads).
 inline bool step_tiled_two(const DevTiles &t, int block) { return t.nl_max > block || t.nf_max > block; }
+inline bool step_tiled_fits(const DevTiles &t, int block)
+{
+    return t.na_max <= block && t.nl_max <= 2 * block && t.nf_max <= 2 * block;
+}
 // Threads of the fused step where the caller leaves them to the library: four
 // waves a tile while all tiles are on the chip at once (three per CU in FP64:
 // a 45,000-cell mesh takes 8.0 us a step, with two waves 8.3), two beyond (a
