@@ -321,6 +321,10 @@ int sdugks_debug_poison(sdugks_t *h, int32_t cell, int32_t i);
 /* Failure injection for tests: the batch's next table rebuild fails with
  * SDUGKS_ENOMEM (nothing is allocated). */
 int sdugks_debug_batch_fail(sdugks_batch_t *b);
+/* For tests: the n >= 0 reciprocals y[k] = 1 / x[k] of positive normal numbers
+ * as the steps form them of densities, on the current device (host arrays).
+ * They are those of an FP64 division. */
+int sdugks_debug_reciprocal(int32_t n, const double *x, double *y);
 
 #ifdef __cplusplus
 }

@@ -919,6 +919,22 @@ int sdugks_debug_poison(sdugks_t *h, int32_t cell, int32_t i)
     return sync_check(h);
 }
 
+int sdugks_debug_reciprocal(int32_t n, const double *x, double *y)
+{
+    if (n < 0 || (n > 0 && (!x || !y))) return fail(SDUGKS_EINVAL, "bad arguments");
+    if (n == 0) return SDUGKS_OK;
+    struct Buffer {                       // freed on every return path
+        double *p = nullptr;
+        ~Buffer() { if (p) (void)hipFree(p); }
+    } b;
+    const size_t bytes = (size_t)n * sizeof(double);
+    if (hipMalloc((void **)&b.p, 2 * bytes) != hipSuccess) return fail(SDUGKS_ENOMEM, "hipMalloc failed");
+    HIPCHK(hipMemcpy(b.p, x, bytes, hipMemcpyHostToDevice));
+    HIPCHK(launch_reciprocal(n, b.p, b.p + n, nullptr));
+    HIPCHK(hipMemcpy(y, b.p + n, bytes, hipMemcpyDeviceToHost));
+    return SDUGKS_OK;
+}
+
 namespace {
 
 const char *const kBatchFailedMsg =

@@ -280,6 +280,8 @@ hipError_t launch_state_io(StateMove move, const StateLayout &l, int c0, int n, 
 // The same f (as stored) and W in every cell, G = 0, snapshot = its velocity.
 hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3, double *f, float *f32, double *W,
                               double *G, double *snap, hipStream_t st);
+// y = 1 / x as the steps form it of their densities.
+hipError_t launch_reciprocal(int n, const double *x, double *y, hipStream_t st);
 // *p = NaN, p pointing at a double (bytes 8) or a float (bytes 4): failure injection.
 hipError_t launch_poke_nan(void *p, int bytes, hipStream_t st);
 

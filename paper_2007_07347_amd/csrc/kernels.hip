@@ -22,6 +22,7 @@
 // exactly and each face flux leaves one cell exactly as it enters the other.
 #include "device.h"
 
+#include "cart_math.h"
 #include "d2q9.h"
 #include "reduce.h"
 
@@ -350,6 +351,12 @@ __global__ void __launch_bounds__(256) k_set_uniform(int nc, int np, Uniform u, 
     snap[(size_t)np + c] = u.W[2] / u.W[0];
 }
 
+__global__ void __launch_bounds__(256) k_reciprocal(int n, const double *x, double *y)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) y[t] = recip(x[t]);
+}
+
 __global__ void k_poke_nan(void *p, int bytes)
 {
     if (bytes == 8) *reinterpret_cast<double *>(p) = __builtin_nan("");
@@ -423,6 +430,12 @@ hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3
     for (int i = 0; i < 9; i++) u.f[i] = f9[i];
     for (int i = 0; i < 3; i++) u.W[i] = W3[i];
     hipLaunchKernelGGL(k_set_uniform, dim3((nc + 255) / 256), dim3(256), 0, st, nc, np, u, f, f32, W, G, snap);
+    return hipGetLastError();
+}
+
+hipError_t launch_reciprocal(int n, const double *x, double *y, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_reciprocal, dim3((n + 255) / 256), dim3(256), 0, st, n, x, y);
     return hipGetLastError();
 }
 

@@ -72,6 +72,7 @@ _sig = {
     "sdugks_debug_batch_fail": [_P],
     "sdugks_batch_destroy": [_P],
     "sdugks_debug_poison": [_P, C.c_int32, C.c_int32],
+    "sdugks_debug_reciprocal": [C.c_int32, _P, _P],
 }
 for _name, _args in _sig.items():
     _fn = getattr(_lib, _name)
@@ -154,6 +155,14 @@ def state_bytes(mesh, bcs, **kw):
     b = C.c_size_t()
     _check(_lib.sdugks_state_bytes(*inp.args(), C.byref(b)))
     return b.value
+
+
+def debug_reciprocal(x):
+    """1 / x of positive normal numbers as the steps form it of densities."""
+    x = np.ascontiguousarray(x, dtype=np.float64).ravel()
+    y = np.empty_like(x)
+    _check(_lib.sdugks_debug_reciprocal(len(x), _ptr(x), _ptr(y)))
+    return y
 
 
 class Solver:
