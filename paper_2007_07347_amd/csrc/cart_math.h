@@ -183,28 +183,49 @@ __device__ __forceinline__ R slope(R wm, R wp, R dm, R dp)
     return fma_(wp, dp, (-wm) * dm);
 }
 
-// fbar+ carried back along every velocity: fbar+_i - dt (e_i . gradient).
+// Reconstruction at the foot points x_f - e dt, as two steps: carried() serves
+// the faces along axis AX, sides() adds what differs from face to face.  In FP32
+// carried() holds fbar+_i - dt e_t g_t, the part across the axis, and along it a
+// velocity's offset h - e dt from the centre is taken in one piece: dt e g first
+// and h g after is rounded once more in between, up to an ulp of the slopes' part.
+// In FP64 that is no part of any error that shows, and carried() holds both
+// parts, alike for the two axes (half the registers: the FP64 march has none left,
+// and took 2 to 3 % more with the other order).
 template <typename R>
-__device__ __forceinline__ void carry_back(R rdt, const R fb[9], const R gx[9], const R gy[9], R b[9])
+constexpr bool kOneOffset = std::is_same<R, float>::value;
+template <int AX, typename R>
+__device__ __forceinline__ void carried(R rdt, const R fb[9], const R gx[9], const R gy[9], R b[9])
 {
     static_for<9>([&](auto I) {
         constexpr int i = I;
         R v = fb[i];
-        if constexpr (cEx[i] != 0) v = fma_(cEx[i] > 0 ? -rdt : rdt, gx[i], v);
-        if constexpr (cEy[i] != 0) v = fma_(cEy[i] > 0 ? -rdt : rdt, gy[i], v);
+        if constexpr (cEx[i] != 0 && (AX == 1 || !kOneOffset<R>)) v = fma_(cEx[i] > 0 ? -rdt : rdt, gx[i], v);
+        if constexpr (cEy[i] != 0 && (AX == 0 || !kOneOffset<R>)) v = fma_(cEy[i] > 0 ? -rdt : rdt, gy[i], v);
         b[i] = v;
     });
 }
 
-// The two sides of a cell along axis AX: offsets hm, hp of its lower and upper
-// face from the centre, b as carry_back, g the slopes along the axis.
-template <int AX, typename R>
-__device__ __forceinline__ void sides(R hm, R hp, const R b[9], const R g[9], Side<R> &lower, Side<R> &upper)
+// fbar+ carried back along the whole of the k-th velocity that enters a cell on
+// its lower (LOWER) or upper side along axis AX: b as carried(), g the slopes
+// along the axis.
+template <int AX, bool LOWER, typename R>
+__device__ __forceinline__ R entering(R rdt, const R b[9], const R g[9], int k)
 {
+    const int i = LOWER ? cP[AX][k] : cN[AX][k];
+    if constexpr (kOneOffset<R>) return fma_(LOWER ? -rdt : rdt, g[i], b[i]);
+    else return b[i];
+}
+
+// The two sides of a cell along axis AX: offsets hm, hp of its lower and upper
+// face from the centre, b as carried(), g the slopes along the axis.
+template <int AX, typename R>
+__device__ __forceinline__ void sides(R rdt, R hm, R hp, const R b[9], const R g[9], Side<R> &lower, Side<R> &upper)
+{
+    const R lo = kOneOffset<R> ? hm + rdt : hm, up = kOneOffset<R> ? hp - rdt : hp;
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-        upper.c[k] = fma_(hp, g[cP[AX][k]], b[cP[AX][k]]);
-        lower.c[k] = fma_(hm, g[cN[AX][k]], b[cN[AX][k]]);
+        upper.c[k] = fma_(up, g[cP[AX][k]], b[cP[AX][k]]);
+        lower.c[k] = fma_(lo, g[cN[AX][k]], b[cN[AX][k]]);
     }
     const R sb = b[cT[AX][0]] + (b[cT[AX][1]] + b[cT[AX][2]]), sg = g[cT[AX][0]] + (g[cT[AX][1]] + g[cT[AX][2]]);
     const R db = b[cT[AX][1]] - b[cT[AX][2]], dg = g[cT[AX][1]] - g[cT[AX][2]];

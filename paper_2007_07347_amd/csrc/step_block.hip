@@ -214,10 +214,11 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
                 }
             }
         }
-        R bk[9];
-        carry_back(c.dt, fb, gx, gy, bk);
+        R bkx[9], bky[9];
+        carried<0>(c.dt, fb, gx, gy, bkx);
+        carried<1>(c.dt, fb, gx, gy, bky);
         Side<R> lower, upper;
-        sides<1>(hb, ht, bk, gy, lower, upper);
+        sides<1>(c.dt, hb, ht, bky, gy, lower, upper);
 #pragma unroll
         for (int e = 0; e < 3; e++) sup[e * NT + tid] = upper.c[e];
         sup[3 * NT + tid] = upper.s;
@@ -226,14 +227,14 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         Outflow acc;
         {
             Side<R> left, right;
-            sides<0>(hl, hr, bk, gx, left, right);
+            sides<0>(c.dt, hl, hr, bkx, gx, left, right);
             Side<R> nb{{ln.next(left.c[0]), ln.next(left.c[1]), ln.next(left.c[2])}, ln.next(left.s), ln.next(left.d)};
             if (any_x) {
 #pragma unroll
                 for (int e = 0; e < 3; e++) {
-                    const R v = ln.next(bk[cP[0][e]] - dl[e]);
+                    const R v = ln.next(entering<0, true>(c.dt, bkx, gx, e) - dl[e]);
                     right.c[e] = ghost_l ? v : right.c[e];
-                    nb.c[e] = wall_r ? bk[cN[0][e]] + dr[e] : nb.c[e];
+                    nb.c[e] = wall_r ? entering<0, false>(c.dt, bkx, gx, e) + dr[e] : nb.c[e];
                 }
                 right.s = ghost_l ? nb.s : right.s;
                 right.d = ghost_l ? nb.d : right.d;
@@ -250,7 +251,7 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         // y faces: each thread the one below its cell
         Side<R> top{{sup[dn], sup[NT + dn], sup[2 * NT + dn]}, sup[3 * NT + dn], sup[4 * NT + dn]};
 #pragma unroll
-        for (int e = 0; e < 3; e++) top.c[e] = wall_b ? bk[cP[1][e]] - db[e] : top.c[e];
+        for (int e = 0; e < 3; e++) top.c[e] = wall_b ? entering<1, true>(c.dt, bky, gy, e) - db[e] : top.c[e];
         top.s = wall_b ? lower.s : top.s;
         top.d = wall_b ? lower.d : top.d;
         R p[3], q[3];
@@ -261,7 +262,9 @@ __device__ __forceinline__ void block_steps(const DevMesh &m, const DevCart &cg,
         R pw[3], qw[3];
         if (any_t) {
             // the face between the last row and the upper wall
-            const Side<R> in{{bk[cN[1][0]] + dt[0], bk[cN[1][1]] + dt[1], bk[cN[1][2]] + dt[2]}, upper.s, upper.d};
+            const Side<R> in{{entering<1, false>(c.dt, bky, gy, 0) + dt[0], entering<1, false>(c.dt, bky, gy, 1) + dt[1],
+                              entering<1, false>(c.dt, bky, gy, 2) + dt[2]},
+                             upper.s, upper.d};
             face_flux<PM>(m, upper, in, Cy, Cy * c.k1, Cy * c.k5, pw, qw);
         }
         __syncthreads();

@@ -297,7 +297,7 @@ struct March {
         const bool wall_t = q == khigh - 1;
         if (UPDATE || (q >= j0 - 1 && q > klow)) {
             const R hb = uniform(rq.hb), ht = uniform(rq.ht), wb = uniform(rq.wb), wt = uniform(rq.wt), Cx = uniform(rq.c);
-            R gx[9], gy[9], bk[9], dr[3], dl[3];
+            R gx[9], gy[9], bx[9], by[9], dr[3], dl[3];
 #pragma unroll
             for (int i = 0; i < 9; i++) {
                 const R dp = shift<kNext>(fbp[i]) - fbp[i];
@@ -310,20 +310,21 @@ struct March {
                     if (i == cN[0][e]) dr[e] = dp;
                 }
             }
-            carry_back(c.dt, fbp, gx, gy, bk);
+            carried<0>(c.dt, fbp, gx, gy, bx);
+            carried<1>(c.dt, fbp, gx, gy, by);
             Side<R> lower, upper;
-            sides<1>(hb, ht, bk, gy, lower, upper);
+            sides<1>(c.dt, hb, ht, by, gy, lower, upper);
             if (UPDATE || q >= j0) {
                 // the x faces (of no use for the row after the segment)
                 Side<R> left, right;
-                sides<0>(hl, hr, bk, gx, left, right);
+                sides<0>(c.dt, hl, hr, bx, gx, left, right);
                 Side<R> beside = shift<kNext>(left);
                 if (edge) {
 #pragma unroll
                     for (int e = 0; e < 3; e++) {
-                        const R v = shift<kNext>(bk[cP[0][e]] - dl[e]);
+                        const R v = shift<kNext>(entering<0, true>(c.dt, bx, gx, e) - dl[e]);
                         right.c[e] = ghost_l ? v : right.c[e];
-                        beside.c[e] = wall_r ? bk[cN[0][e]] + dr[e] : beside.c[e];
+                        beside.c[e] = wall_r ? entering<0, false>(c.dt, bx, gx, e) + dr[e] : beside.c[e];
                     }
                     right.s = ghost_l ? beside.s : right.s;
                     right.d = ghost_l ? beside.d : right.d;
@@ -334,7 +335,9 @@ struct March {
                 face_flux<PM>(m, right, beside, Cx, Cx * c.k1, Cx * c.k5, pr, nr);
                 if (!UPDATE && q == klow + 1) {
 #pragma unroll
-                    for (int e = 0; e < 3; e++) top.c[e] = DOWN ? bk[cN[1][e]] + dyp[cN[1][e]] : bk[cP[1][e]] - dyp[cP[1][e]];
+                    for (int e = 0; e < 3; e++)
+                        top.c[e] = DOWN ? entering<1, false>(c.dt, by, gy, e) + dyp[cN[1][e]]
+                                        : entering<1, true>(c.dt, by, gy, e) - dyp[cP[1][e]];
                     top.s = DOWN ? upper.s : lower.s;
                     top.d = DOWN ? upper.d : lower.d;
                 }
@@ -350,7 +353,9 @@ struct March {
                 // the row outside the wall ends the march: its side
                 R in[3];
 #pragma unroll
-                for (int e = 0; e < 3; e++) in[e] = DOWN ? bk[cP[1][e]] - dy[cP[1][e]] : bk[cN[1][e]] + dy[cN[1][e]];
+                for (int e = 0; e < 3; e++)
+                    in[e] = DOWN ? entering<1, true>(c.dt, by, gy, e) - dy[cP[1][e]]
+                                 : entering<1, false>(c.dt, by, gy, e) + dy[cN[1][e]];
                 fb[0] = in[0]; fb[1] = in[1]; fb[2] = in[2];
             }
         }

@@ -11,10 +11,12 @@
 //   phase 2  least-squares slopes of fbar+ (the LLSR normal equations solved
 //            through precomputed weights A^-1 d; boundary states are points at
 //            the face midpoints) for the tile and its first ring, into LDS with
-//            fbar+ carried back along every velocity, b_i = fbar+_i - dt e_i.g_i;
+//            fbar+;
 //   phase 3  one lane per face of the tile's cells: the upwind value of every
-//            velocity at the foot point (Eq. fbpsource), b_i + r.g_i with r from
-//            the upwind cell's centre to the face; face macros and equilibrium,
+//            velocity at the foot point (Eq. fbpsource), fbar+_i + (r - e_i dt).g_i
+//            with r from the upwind cell's centre to the face (one offset: fbar+
+//            carried back first and then to the face is rounded once more in
+//            between, which shows in FP32); face macros and equilibrium,
 //            f at the face (Eq. f_t_n+1) and its mesoscopic fluxes (Eq. MesoFlux)
 //            into LDS, over fbar+;
 //   phase 4  one lane per tile cell: the fluxes of its faces summed in FP64 in the
@@ -83,7 +85,7 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
     const size_t np = (size_t)m.np;
     const int tid = threadIdx.x;
     // LDS: W of the tile cells [3][PT] (faces on a boundary need it), the
-    // boundary table [n_bc]; then b and the slopes (x, y) [PA][9] of the tile and
+    // boundary table [n_bc]; then fbar+ and the slopes (x, y) [PA][9] of the tile and
     // its first ring, cell by cell, and fbar+ [P][9], whose place the fluxes
     // [8][PF] take in phase 3
     double *const sW = smem;
@@ -189,7 +191,7 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
 
     // ---- phase 2
     if (p2) {
-        R gx[9], gy[9], b[9];
+        R gx[9], gy[9];
 #pragma unroll
         for (int i = 0; i < 9; i++) { gx[i] = 0; gy[i] = 0; }
         // neighbours first, without a branch (an empty slot or a boundary point
@@ -218,9 +220,8 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
                 for (int i = 0; i < 9; i++) { gx[i] = fma_((R)w[sl].x, df[i], gx[i]); gy[i] = fma_((R)w[sl].y, df[i], gy[i]); }
             }
         }
-        carry_back(c.dt, fb, gx, gy, b);
 #pragma unroll
-        for (int i = 0; i < 9; i++) sr[tid * 9 + i] = R3{b[i], gx[i], gy[i]};
+        for (int i = 0; i < 9; i++) sr[tid * 9 + i] = R3{fb[i], gx[i], gy[i]};
     }
     __syncthreads();
 
@@ -242,10 +243,12 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
             constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
             sn[k] = cdot<cEx[p], cEy[p]>(lx, ly);
             special = special || sn[k] == (R)0;
-            // of the pair, out leaves the first cell and in the second
+            // of the pair, out leaves the first cell and in, its opposite, the second
             const bool up = sn[k] > (R)0;
             const int io = up ? p : q;
-            const R out = at(c0, ax, ay, io), in = at(c2, bx, by, p + q - io);
+            const R ds = up ? c.dt : -c.dt;
+            const R out = at(c0, ax - cmul<cEx[p]>(ds), ay - cmul<cEy[p]>(ds), io);
+            const R in = at(c2, bx + cmul<cEx[p]>(ds), by + cmul<cEy[p]>(ds), p + q - io);
             fp[k] = up ? out : in;
             fm[k] = up ? in : out;
         });
@@ -257,7 +260,11 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
                 wall_diff<PM>(m, sbc[-2 - c1], sW[c0], sW[PT + c0], sW[2 * PT + c0], df);
                 static_for<4>([&](auto K) {
                     constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
-                    const R ip = sr[c0 * 9 + p].b + df[p], iq = sr[c0 * 9 + q].b + df[q];
+                    auto back = [&](R dt, int i) {
+                        const R3 v = sr[c0 * 9 + i];
+                        return fma_(-dt, cdot<cEx[p], cEy[p]>(v.x, v.y), v.b + df[i]);
+                    };
+                    const R ip = back(c.dt, p), iq = back(-c.dt, q);
                     fm[k] = sn[k] > (R)0 ? iq : fm[k];
                     fp[k] = sn[k] < (R)0 ? ip : fp[k];
                 });
@@ -265,8 +272,9 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
                 // along the face: the mean of both sides
                 static_for<4>([&](auto K) {
                     constexpr int k = K, p = cPair[k][0], q = cPair[k][1];
-                    const R mp = (R)0.5 * (at(c0, ax, ay, p) + at(c2, bx, by, p));
-                    const R mq = (R)0.5 * (at(c0, ax, ay, q) + at(c2, bx, by, q));
+                    const R dx = cmul<cEx[p]>(c.dt), dy = cmul<cEy[p]>(c.dt);
+                    const R mp = (R)0.5 * (at(c0, ax - dx, ay - dy, p) + at(c2, bx - dx, by - dy, p));
+                    const R mq = (R)0.5 * (at(c0, ax + dx, ay + dy, q) + at(c2, bx + dx, by + dy, q));
                     fp[k] = sn[k] == (R)0 ? mp : fp[k];
                     fm[k] = sn[k] == (R)0 ? mq : fm[k];
                 });

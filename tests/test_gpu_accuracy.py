@@ -1,9 +1,16 @@
 """Rounding of the steps' building blocks: the reciprocal of a density is that
-of an FP64 division."""
+of an FP64 division, the reconstruction takes one offset from a cell's centre to
+the foot point."""
 import numpy as np
 import pytest
 
+import meshgen
+
 pytestmark = pytest.mark.gpu
+
+EX = np.array([0, 1, 0, -1, 0, 1, -1, -1, 1], dtype=float)
+EY = np.array([0, 0, 1, 0, -1, 1, 1, -1, -1], dtype=float)
+WGT = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)
 
 
 @pytest.fixture(scope="module")
@@ -27,3 +34,46 @@ def test_reciprocal_of_a_density_is_the_divisions(sd):
     y = sd.debug_reciprocal(x)
     bad = y != 1.0 / x
     assert not bad.any(), (bad.sum(), [float(v).hex() for v in x[bad][:4]])
+
+
+@pytest.mark.parametrize("prec", ["FP64", "FP32DEV"])
+@pytest.mark.parametrize("structured", [0, 1])
+@pytest.mark.parametrize("n", [(8, 8), (32, 16), (256, 256), (768, 640)])
+def test_a_foot_point_at_the_centre_reads_the_cell(sd, n, structured, prec):
+    """Free transport (tau = 1e30) of a random f over a periodic box of squares of
+    side h with dt = h / 2: the four velocities along the axes have their foot
+    points x_f - e dt at the upwind cell's centre, so one step gives
+    f - (f - f_upwind) / 2 whatever the slopes.  The reconstruction's offset from the
+    centre is zero there and adds no rounding: the flux is the stored f exactly,
+    and of the result's two operations in FP64 the second is rounded to the stored
+    form, half an ulp.  What the equilibrium adds is below dt / tau = 1e-31.  fbar+
+    carried back along e dt first and forth by the face's offset after misses
+    that by up to an ulp of the slopes' contribution, several times f's."""
+    nx, ny = n
+    mesh, bcs = meshgen.periodic_box(nx, ny, lx=nx / 16.0, ly=ny / 16.0)
+    h = 1 / 16.0
+    s = sd.Solver(mesh, bcs, tau=1e30, dt=h / 2, precision=getattr(sd, prec), structured=structured)
+    f, _, _ = meshgen.random_state(nx * ny, seed=5, amp=0.3)
+    if prec == "FP32DEV":
+        f = WGT + (f - WGT).astype(np.float32)          # f - w is stored exactly
+        f = f.astype(np.float64)
+    s.set_state(f, np.c_[f.sum(1), f @ EX, f @ EY])
+    f0 = s.state()[0]
+    s.step(1)
+    f1 = s.state()[0]
+    g = sd.geometry(mesh, bcs, tau=1e30, dt=h / 2)
+    s.close()
+    i, j = np.rint(g["cx"] / h - 0.5).astype(int), np.rint(g["cy"] / h - 0.5).astype(int)
+    at = np.empty((nx, ny), int)
+    at[i, j] = np.arange(nx * ny)
+    d0 = f0 - WGT if prec == "FP32DEV" else f0
+    d1 = f1 - WGT if prec == "FP32DEV" else f1
+    for k, (ex, ey) in {1: (1, 0), 2: (0, 1), 3: (-1, 0), 4: (0, -1)}.items():
+        up = at[(i - ex) % nx, (j - ey) % ny]
+        want = d0[:, k] - 0.5 * (d0[:, k] - d0[up, k])
+        # (f read back as w + the stored deviation, w in FP64: an FP64 ulp of f more)
+        tol = 0.5 * np.spacing(np.abs(want).astype(np.float32)) if prec == "FP32DEV" else 0.5 * np.spacing(np.abs(want))
+        tol = 1.000001 * tol.astype(float) + 4 * np.spacing(np.abs(f0[:, k]) + np.abs(f0[up, k]))
+        assert np.all(np.abs(d1[:, k] - want) <= tol), (k, np.max(np.abs(d1[:, k] - want) / tol))
+    # at rest: no flux
+    assert np.all(np.abs(d1[:, 0] - d0[:, 0]) <= 2 * np.spacing(np.abs(f0[:, 0])))
