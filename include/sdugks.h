@@ -243,6 +243,14 @@ int sdugks_info(sdugks_t *h, double *dt, double *tau, int64_t *step, int32_t *n_
 int sdugks_step_profiled(sdugks_t *h, int64_t n, double *avg_ms, const char **names, int32_t max_kernels,
                          int32_t *n_kernels);
 
+/* How the steps of a handle are launched: the form (two-kernel step, tiles of
+ * the general step, or of the structured step the march or boxes of cells), the
+ * threads per workgroup, the steps that one launch takes at most and the
+ * workgroups of a launch (0 for the two-kernel step).  Outputs may be NULL. */
+enum { SDUGKS_FORM_TWO_KERNEL = 0, SDUGKS_FORM_TILES = 1, SDUGKS_FORM_MARCH = 2, SDUGKS_FORM_BOXES = 3 };
+int sdugks_schedule(sdugks_t *h, int32_t *form, int32_t *threads, int32_t *steps, int32_t *groups);
+
+
 int sdugks_destroy(sdugks_t *h);
 
 const char *sdugks_last_error(void);
@@ -295,6 +303,10 @@ int sdugks_batch_step(sdugks_batch_t *b, int64_t n);
  * or velocity gets NaN, refuses further steps, and the call returns
  * SDUGKS_EDIVERGED after filling every entry. */
 int sdugks_batch_residual(sdugks_batch_t *b, double *eps);
+
+/* As sdugks_schedule, of one member inside the batch (its own workgroups). */
+int sdugks_batch_schedule(sdugks_batch_t *b, int32_t member, int32_t *form, int32_t *threads, int32_t *steps,
+                          int32_t *groups);
 int sdugks_batch_destroy(sdugks_batch_t *b);
 
 /* For callers that cannot allocate device memory (code under HIP graph

@@ -897,6 +897,25 @@ int sdugks_info(sdugks_t *h, double *dt, double *tau, int64_t *step, int32_t *n_
     return SDUGKS_OK;
 }
 
+int sdugks_schedule(sdugks_t *h, int32_t *form, int32_t *threads, int32_t *steps, int32_t *groups)
+{
+    if (!h) return fail(SDUGKS_EINVAL, "null handle");
+    int32_t v[4];
+    if (h->blk.threads) {
+        v[0] = SDUGKS_FORM_BOXES; v[1] = h->blk.threads; v[2] = h->kmax; v[3] = h->blk.nbx * h->blk.nby;
+    } else if (h->mb.cart) {
+        v[0] = SDUGKS_FORM_MARCH; v[1] = 64; v[2] = 1; v[3] = cart_groups(h->dc);
+    } else if (h->mb.n_tiles > 0) {
+        v[0] = SDUGKS_FORM_TILES; v[1] = h->block; v[2] = 1; v[3] = h->mb.n_tiles;
+    } else {
+        v[0] = SDUGKS_FORM_TWO_KERNEL; v[1] = 256; v[2] = 1; v[3] = 0;
+    }
+    int32_t *const out[4] = {form, threads, steps, groups};
+    for (int k = 0; k < 4; k++)
+        if (out[k]) *out[k] = v[k];
+    return SDUGKS_OK;
+}
+
 int sdugks_destroy(sdugks_t *h)
 {
     if (!h) return SDUGKS_OK;
@@ -1299,6 +1318,22 @@ int sdugks_batch_step(sdugks_batch_t *b, int64_t n)
         h->step += n;
     }
     if (n & 1) return batch_build(b);          // every member's buffer index flipped
+    return SDUGKS_OK;
+}
+
+int sdugks_batch_schedule(sdugks_batch_t *b, int32_t member, int32_t *form, int32_t *threads, int32_t *steps,
+                          int32_t *groups)
+{
+    if (!b) return fail(SDUGKS_EINVAL, "null batch");
+    if (b->failed) return fail(SDUGKS_EINVAL, kBatchFailedMsg);
+    if (member < 0 || member >= (int32_t)b->members.size()) return fail(SDUGKS_EINVAL, "no such batch member");
+    for (const BatchGroup &g : b->groups) {
+        if (std::find(g.members.begin(), g.members.end(), member) == g.members.end()) continue;
+        if (form) *form = g.form == kGeneral ? SDUGKS_FORM_TILES : (g.form == kMarch ? SDUGKS_FORM_MARCH : SDUGKS_FORM_BOXES);
+        if (threads) *threads = g.form == kMarch ? 64 : g.block;
+        if (steps) *steps = std::max(1, g.plan.K);
+        if (groups) *groups = member_tiles(b->members[member], g);
+    }
     return SDUGKS_OK;
 }
 

@@ -62,12 +62,14 @@ _sig = {
     "sdugks_info": [_P, _P, _P, _P, _P],
     "sdugks_boundary_flux": [_P, C.c_int32, _P, _P, _P],
     "sdugks_step_profiled": [_P, C.c_int64, _P, _P, C.c_int32, _P],
+    "sdugks_schedule": [_P, _P, _P, _P, _P],
     "sdugks_destroy": [_P],
     "sdugks_last_error": [],
     "sdugks_batch_create": [_P, C.c_int32, _P, _P],
     "sdugks_batch_set_members": [_P, _P, C.c_int32],
     "sdugks_batch_step": [_P, C.c_int64],
     "sdugks_batch_residual": [_P, _P],
+    "sdugks_batch_schedule": [_P, C.c_int32, _P, _P, _P, _P],
     "sdugks_residuals_static": [_P, C.c_int32, _P],
     "sdugks_debug_batch_fail": [_P],
     "sdugks_batch_destroy": [_P],
@@ -96,6 +98,15 @@ def _check(rc):
 
 def _ptr(a):
     return C.c_void_p(a.ctypes.data) if a is not None else None
+
+
+FORMS = ("two-kernel", "tiles", "march", "boxes")
+
+
+def _schedule(call, *args):
+    v = [C.c_int32() for _ in range(4)]
+    _check(call(*args, *[C.byref(x) for x in v]))
+    return {"form": FORMS[v[0].value], "threads": v[1].value, "steps": v[2].value, "groups": v[3].value}
 
 
 class _Inputs:
@@ -246,6 +257,11 @@ class Solver:
         _check(_lib.sdugks_info(self._h, C.byref(dt), C.byref(tau), C.byref(st), C.byref(n)))
         return {"dt": dt.value, "tau": tau.value, "step": st.value, "n_cells": n.value}
 
+    def schedule(self):
+        """How the steps are launched: form (one of FORMS), threads per
+        workgroup, steps per launch at most, workgroups."""
+        return _schedule(_lib.sdugks_schedule, self._h)
+
     def poison(self, cell, i):
         _check(_lib.sdugks_debug_poison(self._h, int(cell), int(i)))
 
@@ -316,6 +332,10 @@ class Batch:
             raise err
         self._call(rc)
         return eps
+
+    def schedule(self, k):
+        """How member k's steps are launched in the batch (as Solver.schedule)."""
+        return _schedule(_lib.sdugks_batch_schedule, self._b, int(k))
 
     def debug_fail_next_build(self):
         _check(_lib.sdugks_debug_batch_fail(self._b))

@@ -5,6 +5,8 @@ remainders of strips (60 columns, or multiples of eight) and boxes (16 and 32 ce
 narrower than a box (rows that wrap inside it) and wider ones, two cells along
 an axis.  Small meshes alone take boxes; in one batch with a 640 x 640 cavity
 they take the march; one launch per step (step_eager) takes boxes of one step.
+(Periodic meshes of at most 16 columns are planned apart from the others there
+and take boxes in the batch too.)
 All use the same arithmetic in the same order, so the results are equal bit by
 bit."""
 import sys

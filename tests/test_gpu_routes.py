@@ -1,0 +1,97 @@
+"""Which form a structured mesh's steps take, and the forms against each other
+where boxes have 512 threads: the launches with the most LDS (about 91 KB with FP64
+arithmetic), on several boxes per mesh, in every storage form.  Alone and in a
+batch of its own such a mesh takes boxes; beside a 640 x 640 cavity it takes the
+march (a periodic channel of at most 16 columns never does: those are planned apart
+from the other members, and boxes are always the better there); launch by launch
+it takes boxes of one step.  All are equal bit by bit."""
+import numpy as np
+import pytest
+
+import meshgen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sd():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2007_07347_amd import sdugks
+    return sdugks
+
+
+def _rect(nx, ny):
+    mesh = meshgen.structured(meshgen.tanh_nodes(nx), meshgen.tanh_nodes(ny), 0, 0, 1, 0)
+    return mesh, [meshgen.bc(meshgen.WALL), meshgen.bc(meshgen.WALL, u=0.1)]
+
+
+# mesh, and the storage forms in which it takes boxes of 512 threads
+WIDE = ("FP64", "FP32NEQ")
+SHAPES = [
+    (_rect, (301, 120), ("FP64", "FP32DEV", "FP32NEQ")),
+    (_rect, (200, 200), ("FP64", "FP32DEV", "FP32NEQ")),
+    (_rect, (301, 301), WIDE),
+    (meshgen.periodic_box, (210, 200), ("FP64", "FP32DEV", "FP32NEQ")),
+    (meshgen.couette, (400, 400), WIDE),
+]
+
+
+@pytest.mark.parametrize("prec", ["FP64", "FP32DEV", "FP32NEQ"])
+@pytest.mark.parametrize("scheme,macro", [(0, 1), (0, 0), (1, 1)])
+def test_boxes_of_512_threads(sd, prec, scheme, macro):
+    kw = dict(cfl=0.5 if macro else 0.1, precision=getattr(sd, prec), macro=macro, scheme=scheme)
+
+    def make(mesh, bcs, seed):
+        s = sd.Solver(mesh, bcs, nu=4e-3 if macro else 2e-2, **kw)
+        f, W, G = meshgen.random_state(s.n_cells, seed=seed, amp=0.02)
+        if macro:
+            G[:] = 0.0
+        s.set_state(f, W, G)
+        return s
+
+    chosen = [(mk, n) for mk, n, precs in SHAPES if prec in precs]
+    problems = [mk(*n) for mk, n in chosen]
+    alone, eager, single, beside = ([make(*p, k) for k, p in enumerate(problems)] for _ in range(4))
+    big = make(*meshgen.cavity(640), 99)
+    b = sd.Batch(beside + [big])
+    b.step(22)
+    b.step(1)
+    for k, (_, n) in enumerate(chosen):
+        print(prec, scheme, macro, n, alone[k].schedule(), b.schedule(k), flush=True)
+        assert alone[k].schedule()["form"] == "boxes" and alone[k].schedule()["threads"] == 512
+        assert alone[k].schedule()["groups"] > 1
+        assert b.schedule(k)["form"] == "march"
+        one = sd.Batch([single[k]])
+        assert one.schedule(0) == alone[k].schedule()
+        one.step(22)
+        one.step(1)
+        one.close()
+        alone[k].step(23)
+        eager[k].step_eager(23)
+        x = alone[k].state()
+        assert all(np.isfinite(v).all() for v in x)
+        for other in (eager[k], single[k], beside[k]):
+            assert all(np.array_equal(v, w) for v, w in zip(x, other.state())), n
+    b.close()
+    for s in alone + eager + single + beside + [big]:
+        s.close()
+
+
+def test_schedules_of_the_other_forms(sd):
+    """Tiles, the two-kernel step and whole meshes in one box; refused calls."""
+    mesh, bcs = meshgen.cavity(40)
+    s = sd.Solver(mesh, bcs, nu=1e-3, structured=1, tile_cells=32, block_threads=128)
+    assert s.schedule() == {"form": "tiles", "threads": 128, "steps": 1, "groups": 50}
+    t = sd.Solver(mesh, bcs, nu=1e-3, tile_cells=-1)
+    assert t.schedule()["form"] == "two-kernel"
+    w = sd.Solver(*meshgen.couette(4, 32), nu=1e-2)
+    assert w.schedule() == {"form": "boxes", "threads": 128, "steps": 1000, "groups": 1}
+    b = sd.Batch([s, w])
+    assert b.schedule(0)["form"] == "tiles" and b.schedule(1)["form"] == "boxes"
+    for k in (-1, 2):
+        with pytest.raises(sd.SdugksError):
+            b.schedule(k)
+    b.close()
+    for x in (s, t, w):
+        x.close()
