@@ -432,7 +432,7 @@ def converge_form(sdugks, meshgen, names=CONVERGE_CASES, tol=1e-8, interval=RESI
     import torch
     cases = {"cavity256_re1000": (lambda: meshgen.cavity(256, beta=1.5, U=0.1), dict(nu=1e-4, cfl=0.5, structured=2)),
              "cylinder200k_re40": (lambda: meshgen.cylinder_ogrid(400, 250, seed=0),
-                                   dict(nu=0.1 / 40, cfl=0.5, u0=0.1, tile_cells=64, block_threads=256))}
+                                   dict(nu=0.1 / 40, cfl=0.5, u0=0.1, tile_cells=64))}
     out = {"rule": f"velocity residual below {tol:g}, checked every {interval} steps; the FP32 deviation form "
                    "runs alongside FP64 for its steps, the FP32 non-equilibrium form on to the rule (cap 1.5x FP64)",
            "cases": {}}
@@ -644,7 +644,7 @@ def large_form(sdugks, meshgen, n=2048, steps=100, warmup=20):
     mesh, bcs = meshgen.cavity(n, beta=1.5, U=0.1)
     out = {"workload": f"lid-driven cavity {n}x{n} tanh(1.5) quads, Re 1000, CFL 0.5, general step on tiles of "
                        f"64 cells and structured step, {steps} steps after {warmup}"}
-    general = {"tile_cells": 64, "block_threads": 256, "structured": 1}
+    general = {"tile_cells": 64, "block_threads": 0, "structured": 1}
     forms = [(sdugks.FP64, "f64", general), (sdugks.FP32DEV, "fp32dev", general),
              (sdugks.FP64, "structured_f64", {"structured": 2}),
              (sdugks.FP32DEV, "structured_fp32dev", {"structured": 2})]

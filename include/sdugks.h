@@ -128,8 +128,8 @@ typedef struct {
                                      polygons of more than four faces or more than 64 boundary-condition
                                      entries always take the two-kernel step) */
     int32_t block_threads;        /* threads per workgroup of the fused step: 64, 128 or 256 (0 = the library's
-                                     choice, and 256 a bound on it: 256 while all tiles are on the chip
-                                     at once, else 128 where the tiles fit) */
+                                     choice: 256 while all tiles are on the chip at once, else 128; on many
+                                     tiles a workgroup of 128 or 256 threads takes two at a time) */
     int32_t scheme;               /* SDUGKS_SCHEME_SIMPLIFIED (default) or SDUGKS_SCHEME_ORIGINAL */
     int32_t structured;           /* structured step for tensor-product quad meshes (the cells are the
                                      rectangles of two coordinate arrays; periodic sides glued row to row

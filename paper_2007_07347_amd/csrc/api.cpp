@@ -137,7 +137,7 @@ struct sdugks_s {
     bool diverged = false;
     int precision = SDUGKS_FP64, macro = SDUGKS_MACRO_CURRENT, scheme = SDUGKS_SCHEME_SIMPLIFIED;
     double rho0 = 1.0;
-    int block = 0;               // threads of the general step
+    int block = 0, per = 0;      // threads of the general step: of a workgroup, of a tile
     bool own_block = false;      // ... the library's choice
     DevMesh dm{};
     DevTiles dt{};
@@ -178,7 +178,8 @@ struct BatchGroup {
     int D = 4, mode = 0, block = 64;
     StepForm form = kGeneral;
     int narrow = 0;
-    bool own_block = true, two = false;     // general step: the library's choice of threads; second cells or faces
+    int per = 0;                      // general step: threads of a tile
+    bool own_block = true, two = false;     // ... the library's choice of threads; second cells or faces
     CartPlan plan;
     size_t lds = 0;
     int n_inst = 0, n_tiles = 0, cap_inst = 0, cap_tiles = 0;
@@ -298,7 +299,7 @@ int launch_step_at(sdugks_t *h, int c, hipStream_t st, GraphChain *gc = nullptr,
     } else if (h->mb.cart) {
         HIPCHK(launch_step_cart(h->dm, h->dc, s, lagged, h->precision, st, gc));
     } else if (h->mb.n_tiles > 0) {
-        HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, st, gc));
+        HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, h->per, st, gc));
     } else {
         DevScratch x = h->scratch();
         HIPCHK(launch_grad(h->dm, s, x, st, gc));
@@ -581,10 +582,9 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
         h->dt.na_max = mb.na_max;
         h->dt.nt_max = mb.nt_max;
         h->dt.nf_max = std::max<int32_t>(1, mb.nf_max);
-        // 256 is a bound rather than a wish: many tiles of 64 quads take 643 us a step with one
-        // item per thread (2048 x 2048 cells, FP64) and 463 on half the threads
-        h->own_block = h->block == 0 || (h->block == 256 && step_tiled_fits(h->dt, 128));
-        if (h->own_block) h->block = step_tiled_block(h->dt, mb.n_tiles);
+        h->own_block = h->block == 0;
+        if (h->own_block) h->block = h->per = step_tiled_block(h->dt, mb.n_tiles);
+        else h->per = step_tiled_per(h->dt, h->block, mb.n_tiles);
         h->dt.hdr = h->at<int32_t>(L.off_thdr);
         h->dt.lgid = h->at<int32_t>(L.off_lgid);
         h->dt.ladj = h->at<int16_t>(L.off_ladj);
@@ -823,7 +823,7 @@ int sdugks_step_profiled(sdugks_t *h, int64_t n, double *avg_ms, const char **na
             if (rc) return rc;
             HIPCHK(hipEventRecord(ev[1], h->stream));
         } else if (tiled) {
-            HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, h->stream));
+            HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, h->per, h->stream));
             HIPCHK(hipEventRecord(ev[1], h->stream));
         } else {
             DevScratch x = h->scratch();
@@ -906,7 +906,7 @@ int sdugks_schedule(sdugks_t *h, int32_t *form, int32_t *threads, int32_t *steps
     } else if (h->mb.cart) {
         v[0] = SDUGKS_FORM_MARCH; v[1] = 64; v[2] = 1; v[3] = cart_groups(h->dc);
     } else if (h->mb.n_tiles > 0) {
-        v[0] = SDUGKS_FORM_TILES; v[1] = h->block; v[2] = 1; v[3] = h->mb.n_tiles;
+        v[0] = SDUGKS_FORM_TILES; v[1] = h->block; v[2] = 1; v[3] = (int32_t)(((int64_t)h->mb.n_tiles * h->per + h->block - 1) / h->block);
     } else {
         v[0] = SDUGKS_FORM_TWO_KERNEL; v[1] = 256; v[2] = 1; v[3] = 0;
     }
@@ -1057,14 +1057,19 @@ int batch_build_tables(sdugks_batch_t *b)
             g.block = 256;
             for (int k : g.members) g.block = std::min(g.block, step_tiled_block(b->members[k]->dt, g.n_tiles));
         }
-        for (int k : g.members) g.two = g.two || step_tiled_two(b->members[k]->dt, g.block);
+        g.per = g.block;
+        if (!g.own_block) {
+            g.per = g.block / 2;
+            for (int k : g.members) g.per = std::max(g.per, step_tiled_per(b->members[k]->dt, g.block, g.n_tiles));
+        }
+        for (int k : g.members) g.two = g.two || step_tiled_two(b->members[k]->dt, g.per);
     }
     bool reuse = want.size() == b->groups.size();
     for (size_t k = 0; reuse && k < want.size(); k++) {
         const BatchGroup &o = b->groups[k], &n = want[k];
         reuse = o.D == n.D && o.mode == n.mode && o.form == n.form && o.narrow == n.narrow && o.lds >= n.lds && o.cap_inst >= n.n_inst &&
                 o.cap_tiles >= n.n_tiles &&
-                o.block == n.block && o.two == n.two && o.plan.K == n.plan.K;
+                o.block == n.block && o.per == n.per && o.two == n.two && o.plan.K == n.plan.K;
     }
     if (!reuse) {
         batch_release_graph(b);
@@ -1160,7 +1165,7 @@ hipError_t batch_launch(sdugks_batch_t *b, const BatchGroup &g, int steps, int p
 {
     const BatchTable tab{g.d_inst, g.d_tmap};
     if (g.form == kGeneral)
-        return launch_step_batch(tab, g.D, g.mode, g.two, parity, g.cap_tiles, g.lds, g.block, b->stream, gc);
+        return launch_step_batch(tab, g.D, g.mode, g.two, parity, g.cap_tiles, g.lds, g.block, g.per, b->stream, gc);
     if (g.form == kMarch) return launch_step_batch_cart(tab, g.mode, parity, g.cap_tiles, g.lds, b->stream, gc);
     return launch_step_batch_block(tab, g.form == kBoxesWrap, g.block, g.mode, steps, parity, g.cap_tiles, g.lds,
                                    b->stream, gc);
@@ -1332,7 +1337,8 @@ int sdugks_batch_schedule(sdugks_batch_t *b, int32_t member, int32_t *form, int3
         if (form) *form = g.form == kGeneral ? SDUGKS_FORM_TILES : (g.form == kMarch ? SDUGKS_FORM_MARCH : SDUGKS_FORM_BOXES);
         if (threads) *threads = g.form == kMarch ? 64 : g.block;
         if (steps) *steps = std::max(1, g.plan.K);
-        if (groups) *groups = member_tiles(b->members[member], g);
+        const int32_t tiles = member_tiles(b->members[member], g), at_once = g.form == kGeneral ? g.block / g.per : 1;
+        if (groups) *groups = (tiles + at_once - 1) / at_once;
     }
     return SDUGKS_OK;
 }

@@ -181,11 +181,16 @@ hipError_t launch_grad(const DevMesh &m, const DevState &s, const DevScratch &x,
                        GraphChain *gc = nullptr);
 hipError_t launch_flux_update(const DevMesh &m, const DevState &s, const DevScratch &x, int lagged, hipStream_t st,
                               GraphChain *gc = nullptr);
-// Fused one-kernel step over tiles (D <= 4 slots per cell).
+// Threads and LDS of one tile in a workgroup that has one or two.
+struct TileShare {
+    int32_t threads, bytes;
+};
+// Fused one-kernel step over tiles (D <= 4 slots per cell), workgroups of `block`
+// threads with `per` of them to a tile (block or half of it).
 // mode: 0 FP64; 1 FP32 storage of f - w_i rho0, FP32 face arithmetic; 2 FP32
 // storage of f - feq(W), FP64 arithmetic.
 hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState &s, int lagged, int mode,
-                             int block, hipStream_t st, GraphChain *gc = nullptr);
+                             int block, int per, hipStream_t st, GraphChain *gc = nullptr);
 size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc);
 // More local cells or faces than threads (never more than twice as many, nor
 // more cells of tile and first ring than threads).
@@ -201,6 +206,13 @@ inline bool step_tiled_fits(const DevTiles &t, int block)
 inline int step_tiled_block(const DevTiles &t, int64_t n_tiles)
 {
     return n_tiles <= 768 && !step_tiled_two(t, 256) ? 256 : 128;
+}
+// Threads per tile of a workgroup whose threads the caller gives: half of them,
+// and two tiles at a time, beyond as many tiles as the chip takes at once, where
+// half the waves do more with a tile (one or two tiles: see k_step_tiled)
+inline int step_tiled_per(const DevTiles &t, int block, int64_t n_tiles)
+{
+    return block > 64 && n_tiles > 768 * 256 / block && step_tiled_fits(t, block / 2) ? block / 2 : block;
 }
 // Structured step of a tensor-product quad mesh, marching form (a wave per
 // segment of a strip of columns), and below its batched form (members of one
@@ -225,8 +237,8 @@ inline int32_t cart_groups(const DevCart &c) { return c.strips * c.segs; }
 hipError_t launch_step_batch_cart(const BatchTable &tab, int mode, int parity, int cap_tiles, size_t lds,
                                   hipStream_t st, GraphChain *gc = nullptr);
 // Batched fused step over the tiles of all members (same D class and mode).
-hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds,
-                             int block, hipStream_t st, GraphChain *gc = nullptr);
+hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds_tile,
+                             int block, int per, hipStream_t st, GraphChain *gc = nullptr);
 // Deterministic reductions of the residual / mass / finiteness check: writes
 // out4 = {sum |u-u_snap|^2, sum |u_snap|^2, sum V rho, count of non-finite}.
 // snap = [2][np] (U, V); update_snap re-snapshots.

@@ -68,10 +68,12 @@ namespace {
 // Opposite velocities: pair k is cPair[k][0] and cPair[k][1].
 constexpr int cPair[4][2] = {{1, 3}, {2, 4}, {5, 7}, {6, 8}};
 
-// One time step of tile t of one instance (the whole workgroup takes part).  TWO:
-// more local cells or faces than threads, so threads take second ones.
+// One time step of tile t of one instance by the threads of its place (B of them,
+// smem its LDS), whose results are written where live.  TWO: more local cells or
+// faces than threads, so threads take second ones.
 template <int D, int PM, bool TWO>
-__device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, const DevState &s, int lagged, int t)
+__device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, const DevState &s, int lagged, int t,
+                                          int tid, int B, double *smem, bool live)
 {
     using R = Arith<PM>;                        // arithmetic of fbar+, slopes, faces
     using V = Stored<PM>;
@@ -80,10 +82,8 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
     struct R3 {
         R b, x, y;
     };
-    extern __shared__ double smem[];
     const int P = tl.nl_max, PA = tl.na_max, PT = tl.nt_max, PF = tl.nf_max;
     const size_t np = (size_t)m.np;
-    const int tid = threadIdx.x;
     // LDS: W of the tile cells [3][PT] (faces on a boundary need it), the
     // boundary table [n_bc]; then fbar+ and the slopes (x, y) [PA][9] of the tile and
     // its first ring, cell by cell, and fbar+ [P][9], whose place the fluxes
@@ -100,7 +100,6 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
     // pitches, not the tile's own counts: every padded entry is a valid filler
     // (cell 0, no neighbour, zero weight, empty face), so no request waits for
     // the tile header, whose counts only mask what lanes without work read.
-    const int B = (int)blockDim.x;
     // element i of a table (its base a scalar, the offset 32 bits)
     auto ld = [](const auto *base, int i) {
         using E = std::remove_const_t<std::remove_pointer_t<decltype(base)>>;
@@ -307,7 +306,7 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
     __syncthreads();
 
     // ---- phase 4
-    if (!p4) return;
+    if (!p4 || !live) return;
     Outflow o;
 #pragma unroll
     for (int i = 0; i < 9; i++) o.F[i] = 0.0;
@@ -337,55 +336,82 @@ __device__ __forceinline__ void step_tile(const DevMesh &m, const DevTiles &tl, 
         for (int k = 0; k < 3; k++) gout(s.Go)[k * np + g1] = G[k];
 }
 
-// Workgroups are dealt round-robin to the XCDs: block b runs on XCD b % 8.
-// Give XCD x the contiguous range [x * per, (x + 1) * per) of a sequence of
-// slots (the grid a multiple of 8).
-__device__ __forceinline__ int xcd_tile(int n)
-{
-    const int per = (n + kXcds - 1) / kXcds;
-    return (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
-}
-
 // Waves on a SIMD that the registers are bound to allow.
 template <int PM, bool TWO>
 constexpr int kTiledWaves = PM == SDUGKS_FP32DEV ? 4 : (TWO ? 2 : 3);
 
-// One block per tile: the tile of this block, XCD by XCD in contiguous ranges
-// (xcd_range_start).  It follows from the block index and the grid size
-// alone, so the first requests wait for nothing but the table pointers.
-template <int D, int PM, bool TWO>
-__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_tiled(DevMesh m, DevTiles tl, DevState s, int lagged)
+// A workgroup's tiles: one, or (PAIR) two side by side on half of its threads each
+// and on LDS of their own, which go through the barriers together.  Two tiles
+// on 256 threads do what one on 128 does: 1024 x 1024 quads in tiles of 64, 32
+// and 16 cells on 256, 128 and 128 threads take 129, 129 and 146 us a step in FP64
+// (one tile per workgroup 176, 166 and 266), 200,000 triangles 22.7, 23.3 and 27.5.
+template <bool PAIR>
+struct Place {
+    int sub = 0, tid;                   // which of them this thread works on, its index there
+    double *smem;
+    __device__ __forceinline__ explicit Place(const TileShare &sh)
+    {
+        extern __shared__ double lds[];
+        tid = (int)threadIdx.x;
+        smem = lds;
+        if constexpr (PAIR) {
+            sub = __builtin_amdgcn_readfirstlane(tid >= sh.threads ? 1 : 0);
+            tid -= sub * sh.threads;
+            smem += sub * (sh.bytes / 8);
+        }
+    }
+};
+
+// The tiles of this block, XCD by XCD in contiguous ranges (xcd_range_start).  They
+// follow from the block index and the grid size alone, so the first requests
+// wait for nothing but the table pointers.  Past the last tile the second place
+// repeats it and writes nothing.
+template <int D, int PM, bool TWO, bool PAIR>
+__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_tiled(DevMesh m, DevTiles tl, DevState s, int lagged, TileShare sh)
 {
+    const Place<PAIR> at(sh);
     const int x = (int)(blockIdx.x % kXcds);
-    const int t = xcd_range_start((int)gridDim.x, x) + (int)(blockIdx.x / kXcds);
-    step_tile<D, PM, TWO>(m, tl, s, lagged, t);
+    const int u = xcd_range_start((int)gridDim.x, x) + (int)(blockIdx.x / kXcds);
+    const int t = PAIR ? 2 * u + at.sub : u;
+    const bool live = !PAIR || t < tl.n_tiles;
+    step_tile<D, PM, TWO>(m, tl, s, lagged, live ? t : tl.n_tiles - 1, at.tid, PAIR ? sh.threads : (int)blockDim.x, at.smem, live);
 }
 
 // Batched step: the tiles of all instances form one sequence; the grid covers
-// a fixed capacity and each block reads its member and local tile from the
-// device map (one load; member -1 past the live tiles), so the table can
+// a fixed capacity and each block reads its members and local tiles from the
+// device map (one load each; member -1 past the live tiles), so the table can
 // change between launches of a captured graph.  parity selects each
 // instance's ping-pong buffers: it reads buffer (parity0 ^ parity).  Global
 // memory is reached through global-address-space pointers (gin, gout in
 // step_tile): the members' pointers come from their records, not from
-// kernel arguments.
-template <int D, int PM, bool TWO>
-__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_batch(BatchTable tab, int parity)
+// kernel arguments.  per: slots of an XCD, the live ones at their start.
+template <int D, int PM, bool TWO, bool PAIR>
+__global__ void __launch_bounds__(256, (kTiledWaves<PM, TWO>)) k_step_batch(BatchTable tab, int parity, TileShare sh, int per)
 {
-    // the slot's (member, tile) as one 8-byte load, so that the tile index
+    // a slot's (member, tile) as one 8-byte load, so that the tile index
     // does not wait for the exit test on the member
-    const unsigned long long slot = reinterpret_cast<const unsigned long long *>(tab.tmap)[xcd_tile((int)gridDim.x)];
+    const Place<PAIR> at(sh);
+    const unsigned long long *const map = reinterpret_cast<const unsigned long long *>(tab.tmap) + (int)(blockIdx.x % kXcds) * per;
+    const int j = (PAIR ? 2 : 1) * (int)(blockIdx.x / kXcds);
+    unsigned long long slot = map[j];
+    bool live = true;
+    if (PAIR && at.sub) {
+        // a place past the live tiles goes along with the workgroup's first, writing nothing
+        const unsigned long long second = j + 1 < per ? map[j + 1] : ~0ull;
+        live = (int)(unsigned)second >= 0;
+        slot = live ? second : slot;
+    }
     const int member = (int)(unsigned)slot, tile = (int)(unsigned)(slot >> 32);
     // the member's record copied once: its fields are then requested together
     // (no address depends on another field) and stay in scalar registers
-    // across the barriers instead of being reloaded from memory.  A slot past
+    // across the barriers instead of being reloaded from memory.  A workgroup past
     // the live tiles (member -1) leaves without stepping (the compiler may
     // take that exit before the record is requested).
     const BatchInst &in = tab.inst[member < 0 ? 0 : member];
     const DevMesh m = in.m;
     const DevTiles tl = in.t;
     if (member < 0) return;
-    step_tile<D, PM, TWO>(m, tl, batch_state(in, parity), in.lagged, tile);
+    step_tile<D, PM, TWO>(m, tl, batch_state(in, parity), in.lagged, tile, at.tid, PAIR ? sh.threads : (int)blockDim.x, at.smem, live);
 }
 
 }  // namespace
@@ -395,19 +421,23 @@ size_t step_tiled_lds_bytes(const DevTiles &t, int mode, int n_bc)
     return tile_lds_bytes(t.nl_max, t.na_max, t.nt_max, t.nf_max, n_bc, mode == 1 ? sizeof(float) : sizeof(double));
 }
 
-static unsigned step_tiled_grid(const DevTiles &t) { return (unsigned)t.n_tiles; }
+// LDS of a place: the next one begins on a boundary of 16 bytes.
+static TileShare tile_share(int threads, size_t lds) { return {threads, (int32_t)((lds + 15) / 16 * 16)}; }
 
 // mode: 0 FP64, 1 FP32 deviation with FP32 face arithmetic, 2 FP32
 // storage of f - feq(W) with FP64 arithmetic (the SDUGKS_FP64 / FP32DEV / FP32NEQ values)
 hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState &s, int lagged, int mode,
-                             int block, hipStream_t st, GraphChain *gc)
+                             int block, int per, hipStream_t st, GraphChain *gc)
 {
-    const size_t lds = step_tiled_lds_bytes(t, mode, m.n_bc);
-    const dim3 grid(step_tiled_grid(t)), blk(block);
-    const bool two = step_tiled_two(t, block);
+    const TileShare sh = tile_share(per, step_tiled_lds_bytes(t, mode, m.n_bc));
+    const int tiles = block / per;
+    const size_t lds = (size_t)tiles * sh.bytes;
+    const dim3 grid((unsigned)((t.n_tiles + tiles - 1) / tiles)), blk(block);
+    const bool two = step_tiled_two(t, per);
+#define SDG_K(...) emit(&k_step_tiled<__VA_ARGS__>, grid, blk, lds, st, gc, m, t, s, lagged, sh)
 #define SDG_TILED(DD, PP) \
-    return two ? emit(&k_step_tiled<DD, PP, true>, grid, blk, lds, st, gc, m, t, s, lagged) \
-               : emit(&k_step_tiled<DD, PP, false>, grid, blk, lds, st, gc, m, t, s, lagged)
+    return tiles == 2 ? (two ? SDG_K(DD, PP, true, true) : SDG_K(DD, PP, false, true)) \
+                      : (two ? SDG_K(DD, PP, true, false) : SDG_K(DD, PP, false, false))
     if (m.D <= 3) {
         if (mode == 1) SDG_TILED(3, 1);
         if (mode == 2) SDG_TILED(3, 2);
@@ -417,15 +447,20 @@ hipError_t launch_step_tiled(const DevMesh &m, const DevTiles &t, const DevState
     if (mode == 2) SDG_TILED(4, 2);
     SDG_TILED(4, 0);
 #undef SDG_TILED
+#undef SDG_K
 }
 
-hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds,
-                             int block, hipStream_t st, GraphChain *gc)
+hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, int parity, int cap_tiles, size_t lds_tile,
+                             int block, int per, hipStream_t st, GraphChain *gc)
 {
-    const dim3 grid((unsigned)batch_grid(cap_tiles)), blk(block);
+    const TileShare sh = tile_share(per, lds_tile);
+    const int tiles = block / per, slots = batch_grid(cap_tiles) / kXcds;
+    const size_t lds = (size_t)tiles * sh.bytes;
+    const dim3 grid((unsigned)(kXcds * ((slots + tiles - 1) / tiles))), blk(block);
+#define SDG_K(...) emit(&k_step_batch<__VA_ARGS__>, grid, blk, lds, st, gc, tab, parity, sh, slots)
 #define SDG_BATCH(DD, PP) \
-    return two ? emit(&k_step_batch<DD, PP, true>, grid, blk, lds, st, gc, tab, parity) \
-               : emit(&k_step_batch<DD, PP, false>, grid, blk, lds, st, gc, tab, parity)
+    return tiles == 2 ? (two ? SDG_K(DD, PP, true, true) : SDG_K(DD, PP, false, true)) \
+                      : (two ? SDG_K(DD, PP, true, false) : SDG_K(DD, PP, false, false))
     if (D <= 3) {
         if (mode == 1) SDG_BATCH(3, 1);
         if (mode == 2) SDG_BATCH(3, 2);
@@ -435,6 +470,7 @@ hipError_t launch_step_batch(const BatchTable &tab, int D, int mode, bool two, i
     if (mode == 2) SDG_BATCH(4, 2);
     SDG_BATCH(4, 0);
 #undef SDG_BATCH
+#undef SDG_K
 }
 
 }  // namespace sdg

@@ -95,3 +95,46 @@ def test_schedules_of_the_other_forms(sd):
     b.close()
     for x in (s, t, w):
         x.close()
+
+
+@pytest.mark.parametrize("prec", ["FP64", "FP32DEV", "FP32NEQ"])
+def test_threads_asked_for_are_launched(sd, prec):
+    """Explicit schedules of the general step run on the threads they name.  On more
+    tiles than the chip takes at once (785 of 64 cells, 1569 of 32 and 3138 of 16 here:
+    an odd last tile among them) a workgroup has two tiles; bits as with one tile
+    per workgroup, alone and in a batch beside a smaller mesh of other pitches."""
+    mesh, bcs = meshgen.cylinder_ogrid(251, 100, seed=6)
+    small = meshgen.cylinder_ogrid(40, 12, seed=7, quad_layers=12)
+    ex = np.array([0, 1, 0, -1, 0, 1, -1, -1, 1.0])
+    ey = np.array([0, 0, 1, 0, -1, 1, 1, -1, -1.0])
+
+    def make(mesh, bcs, sched, seed):
+        s = sd.Solver(mesh, bcs, nu=4e-3, cfl=0.4, precision=getattr(sd, prec), **sched)
+        f, _, _ = meshgen.random_state(s.n_cells, seed=seed, amp=0.02)
+        s.set_state(f, np.c_[f.sum(1), f @ ex, f @ ey])
+        return s
+
+    refs = []
+    for m, seed in (((mesh, bcs), 3), (small, 4)):
+        s = make(*m, dict(tile_cells=16, block_threads=64), seed)
+        s.step(7)
+        refs.append(s.state())
+        s.close()
+    for tc, bt, tiles in ((64, 256, 2), (32, 256, 2), (16, 256, 2), (32, 128, 2), (16, 128, 2), (16, 64, 1)):
+        sched = dict(tile_cells=tc, block_threads=bt)
+        s = make(mesh, bcs, sched, 3)
+        v = s.schedule()
+        n = sd.tiling(mesh, bcs, nu=4e-3, cfl=0.4, precision=getattr(sd, prec), **sched)["n_tiles"]
+        print(prec, tc, bt, n, v, flush=True)
+        assert v["form"] == "tiles" and v["threads"] == bt and v["groups"] == -(-n // tiles)
+        s.step(7)
+        members = [make(*small, sched, 4), make(mesh, bcs, sched, 3), make(*small, sched, 4)]
+        b = sd.Batch(members)
+        assert b.schedule(1)["threads"] == bt
+        b.step(7)
+        for x, ref in zip((s, *members), (refs[0], refs[1], refs[0], refs[1])):
+            assert all(np.array_equal(p, q) for p, q in zip(x.state(), ref)), (tc, bt)
+            assert np.isfinite(x.state()[0]).all()
+        b.close()
+        for x in (s, *members):
+            x.close()
