@@ -281,7 +281,8 @@ int sdugks_batch_create(sdugks_t *const *members, int32_t n, void *stream, sdugk
  * allocated (SDUGKS_ENOMEM) or filled (SDUGKS_EHIP), the batch is left with
  * no members and marked failed: sdugks_batch_step and sdugks_batch_residual
  * then return SDUGKS_EINVAL until a later sdugks_batch_set_members succeeds.
- * The same holds for the table refresh inside sdugks_batch_step. */
+ * The same holds for the refresh of the members' buffer indices at the start of
+ * sdugks_batch_step (one small launch where an odd number of launches went before). */
 int sdugks_batch_set_members(sdugks_batch_t *b, sdugks_t *const *members, int32_t n);
 /* Advance every member n >= 0 time steps (asynchronous on the batch stream):
  * per step form (structured or general, precision) a chain of launches of its
@@ -304,9 +305,11 @@ int sdugks_batch_step(sdugks_batch_t *b, int64_t n);
  * SDUGKS_EDIVERGED after filling every entry. */
 int sdugks_batch_residual(sdugks_batch_t *b, double *eps);
 
-/* As sdugks_schedule, of one member inside the batch (its own workgroups). */
+/* As sdugks_schedule, of one member inside the batch (its own workgroups); builds:
+ * how often the batch has planned and filled its tables (at creation and on a
+ * change of members; steps do neither). */
 int sdugks_batch_schedule(sdugks_batch_t *b, int32_t member, int32_t *form, int32_t *threads, int32_t *steps,
-                          int32_t *groups);
+                          int32_t *groups, int32_t *builds);
 int sdugks_batch_destroy(sdugks_batch_t *b);
 
 /* For callers that cannot allocate device memory (code under HIP graph

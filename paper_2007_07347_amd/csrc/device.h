@@ -294,6 +294,13 @@ hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3
                               double *G, double *snap, hipStream_t st);
 // y = 1 / x as the steps form it of their densities.
 hipError_t launch_reciprocal(int n, const double *x, double *y, hipStream_t st);
+// The buffer index (bit k) that each of n members of a batch table reads at parity 0;
+// the bits travel in the kernel arguments.
+constexpr int kParityPack = 1024;
+struct ParityPack {
+    uint32_t bits[kParityPack / 32];
+};
+hipError_t launch_set_parity(BatchInst *inst, int n, const ParityPack &p, hipStream_t st);
 // *p = NaN, p pointing at a double (bytes 8) or a float (bytes 4): failure injection.
 hipError_t launch_poke_nan(void *p, int bytes, hipStream_t st);
 

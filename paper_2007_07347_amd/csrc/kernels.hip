@@ -357,6 +357,12 @@ __global__ void __launch_bounds__(256) k_reciprocal(int n, const double *x, doub
     if (t < n) y[t] = recip(x[t]);
 }
 
+__global__ void __launch_bounds__(256) k_set_parity(BatchInst *inst, int n, ParityPack p)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) inst[k].parity0 = (int32_t)(p.bits[k / 32] >> (k % 32) & 1u);
+}
+
 __global__ void k_poke_nan(void *p, int bytes)
 {
     if (bytes == 8) *reinterpret_cast<double *>(p) = __builtin_nan("");
@@ -436,6 +442,12 @@ hipError_t launch_set_uniform(int nc, int np, const double *f9, const double *W3
 hipError_t launch_reciprocal(int n, const double *x, double *y, hipStream_t st)
 {
     hipLaunchKernelGGL(k_reciprocal, dim3((n + 255) / 256), dim3(256), 0, st, n, x, y);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_parity(BatchInst *inst, int n, const ParityPack &p, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_set_parity, dim3((n + 255) / 256), dim3(256), 0, st, inst, n, p);
     return hipGetLastError();
 }
 

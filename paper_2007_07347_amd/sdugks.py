@@ -69,7 +69,7 @@ _sig = {
     "sdugks_batch_set_members": [_P, _P, C.c_int32],
     "sdugks_batch_step": [_P, C.c_int64],
     "sdugks_batch_residual": [_P, _P],
-    "sdugks_batch_schedule": [_P, C.c_int32, _P, _P, _P, _P],
+    "sdugks_batch_schedule": [_P, C.c_int32, _P, _P, _P, _P, _P],
     "sdugks_residuals_static": [_P, C.c_int32, _P],
     "sdugks_debug_batch_fail": [_P],
     "sdugks_batch_destroy": [_P],
@@ -103,9 +103,9 @@ def _ptr(a):
 FORMS = ("two-kernel", "tiles", "march", "boxes")
 
 
-def _schedule(call, *args):
+def _schedule(call, *args, more=()):
     v = [C.c_int32() for _ in range(4)]
-    _check(call(*args, *[C.byref(x) for x in v]))
+    _check(call(*args, *[C.byref(x) for x in v], *more))
     return {"form": FORMS[v[0].value], "threads": v[1].value, "steps": v[2].value, "groups": v[3].value}
 
 
@@ -335,7 +335,13 @@ class Batch:
 
     def schedule(self, k):
         """How member k's steps are launched in the batch (as Solver.schedule)."""
-        return _schedule(_lib.sdugks_batch_schedule, self._b, int(k))
+        return _schedule(_lib.sdugks_batch_schedule, self._b, int(k), more=(None,))
+
+    def builds(self):
+        """How often the batch has planned and filled its tables."""
+        n = C.c_int32()
+        _check(_lib.sdugks_batch_schedule(self._b, 0, None, None, None, None, C.byref(n)))
+        return n.value
 
     def debug_fail_next_build(self):
         _check(_lib.sdugks_debug_batch_fail(self._b))

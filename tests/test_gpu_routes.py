@@ -138,3 +138,49 @@ def test_threads_asked_for_are_launched(sd, prec):
         b.close()
         for x in (s, *members):
             x.close()
+
+
+@pytest.mark.parametrize("prec", ["FP64", "FP32DEV"])
+def test_odd_steps_do_not_plan_again(sd, prec):
+    """An odd number of batched steps, or of a member's launches alone (a mesh in one
+    box takes any number of steps in one), changes the buffers that members read.
+    The batch keeps its tables; states are those of the members stepped alone, and
+    the batch works on after a change of members with odd indices."""
+    meshes = [meshgen.couette(4, 32), meshgen.cavity(48), meshgen.cylinder_ogrid(40, 12, seed=2), meshgen.couette(6, 20)]
+
+    def make(k):
+        s = sd.Solver(*meshes[k], nu=4e-3, cfl=0.5, precision=getattr(sd, prec))
+        f, W, _ = meshgen.random_state(s.n_cells, seed=k, amp=0.02)
+        s.set_state(f, W)
+        return s
+
+    alone, members = [make(k) for k in range(4)], [make(k) for k in range(4)]
+    b = sd.Batch(members)
+    assert b.builds() == 1
+    total = [0] * 4
+    for n, stepped in ((1, ()), (3, (0,)), (2, (0, 1)), (5, (2, 3)), (1, (0, 1, 2)), (4, ())):
+        for k in stepped:
+            members[k].step(4)
+            total[k] += 4
+        b.step(n)
+        total = [t + n for t in total]
+    assert b.builds() == 1
+    b.set_members(members[1:])
+    assert b.builds() == 2
+    b.step(3)
+    total = [total[0]] + [t + 3 for t in total[1:]]
+    assert b.builds() == 2
+    for s, m, n in zip(alone, members, total):
+        s.step(n)
+        assert m.info()["step"] == n
+        assert all(np.array_equal(x, y) for x, y in zip(s.state(), m.state()))
+    b.debug_fail_next_build()
+    with pytest.raises(sd.SdugksError):
+        b.step(1)
+    with pytest.raises(sd.SdugksError):
+        b.step(2)
+    b.set_members(members)
+    b.step(1)
+    b.close()
+    for s in alone + members:
+        s.close()
