@@ -236,10 +236,13 @@ int sdugks_boundary_flux(sdugks_t *h, int32_t tag, double *faces, double *sum, i
 /* Any output may be NULL. */
 int sdugks_info(sdugks_t *h, double *dt, double *tau, int64_t *step, int32_t *n_cells);
 
-/* Average device duration (milliseconds) of each kernel of the step over the
- * next n steps, measured with HIP events on the handle's stream around every
- * launch (slower than sdugks_step; for profiling).  names: optional array of
- * max_kernels const char* receiving static kernel names.  *n_kernels: count. */
+/* Average device duration per step (milliseconds) of each kernel of the step
+ * over the next n steps, measured with HIP events on the handle's stream around
+ * every launch (slower than sdugks_step; for profiling); a launch takes as many
+ * steps as in sdugks_step.  names: optional array of max_kernels const char*
+ * receiving static kernel names; k_step_cart stands for the structured step in
+ * both of its forms (sdugks_schedule says which: boxes are k_step_block).
+ * *n_kernels: count. */
 int sdugks_step_profiled(sdugks_t *h, int64_t n, double *avg_ms, const char **names, int32_t max_kernels,
                          int32_t *n_kernels);
 

@@ -815,31 +815,30 @@ int sdugks_step_profiled(sdugks_t *h, int64_t n, double *avg_ms, const char **na
     hipEvent_t *ev = evs.e;
     for (int k = 0; k < 3; k++) HIPCHK(hipEventCreate(&ev[k]));
     double acc[2] = {0, 0};
-    for (int64_t k = 0; k < n; k++) {
-        DevState s = h->state();
-        const int lagged = h->macro == SDUGKS_MACRO_LAGGED;
+    for (int64_t done = 0; done < n;) {
+        // as sdugks_step launches them: boxes take up to kmax steps at once
+        const int steps = (int)std::min<int64_t>(n - done, h->kmax);
         HIPCHK(hipEventRecord(ev[0], h->stream));
-        if (h->mb.cart) {
-            int rc = launch_step_at(h, h->cur, h->stream);
+        if (tiled) {
+            int rc = launch_step_at(h, h->cur, h->stream, nullptr, steps);
             if (rc) return rc;
             HIPCHK(hipEventRecord(ev[1], h->stream));
-        } else if (tiled) {
-            HIPCHK(launch_step_tiled(h->dm, h->dt, s, lagged, h->precision, h->block, h->per, h->stream));
-            HIPCHK(hipEventRecord(ev[1], h->stream));
         } else {
+            const DevState s = h->state();
             DevScratch x = h->scratch();
             HIPCHK(launch_grad(h->dm, s, x, h->stream));
             HIPCHK(hipEventRecord(ev[1], h->stream));
-            HIPCHK(launch_flux_update(h->dm, s, x, lagged, h->stream));
+            HIPCHK(launch_flux_update(h->dm, s, x, h->macro == SDUGKS_MACRO_LAGGED, h->stream));
             HIPCHK(hipEventRecord(ev[2], h->stream));
         }
+        h->cur ^= 1;
+        h->step += steps;
+        done += steps;
         HIPCHK(hipEventSynchronize(ev[nk]));
         float a = 0, b = 0;
         HIPCHK(hipEventElapsedTime(&a, ev[0], ev[1]));
         if (!tiled) HIPCHK(hipEventElapsedTime(&b, ev[1], ev[2]));
         acc[0] += a; acc[1] += b;
-        h->cur ^= 1;
-        h->step++;
     }
     for (int k = 0; k < nk; k++) avg_ms[k] = n ? acc[k] / n : 0;
     if (names) {
