@@ -454,11 +454,14 @@ __device__ __forceinline__ void march_unit(const DevMesh &m, const DevCart &cg, 
     const int w = strip + 1 < cg.strips ? cg.strip_w + (strip < cg.strip_more) : cg.nx - i0;
     const int j1 = j0 + cg.seg_h + (seg < cg.seg_more);
     Arith<PM> *const lx = (Arith<PM> *)(bcs + m.n_bc);
-    // Every other segment downwards on meshes whose state the memory-side cache
-    // holds: 1024 x 1024 cells 31.9 -> 30.9 us (FP32 deviations), 46.3 -> 44.4
-    // (FP64); upwards all on larger ones (2048 x 2048: 128.4 against 129.8, FP64
-    // 253 either way) and in FP32NEQ (39.6 against 40.0).
-    if (PM != SDUGKS_FP32NEQ && (seg & 1) && m.nc < (1 << 21))
+    // Every other segment downwards while the state, in and out, is little more than
+    // the memory-side cache's 256 MB.  us a step, upwards all against every other
+    // downwards, by cells an edge: FP64 800 32.3 / 29.2, 1024 45.7 / 43.3, 1152 53.3 /
+    // 51.0, 1280 (315 MB) 77.6 / 77.3, 1448 (403 MB) 100 / 105; FP32 deviations 1024 31.3 / 30.7, 1448 (252 MB) 50.1 / 50.1, 1600 76.0 / 76.0,
+    // 1792 (385 MB) 95.7 / 97.4, 2560 199 / 200; FP32NEQ the same up to 1024 and 2 to 8 %
+    // slower beyond.
+    constexpr int most = (int)(((size_t)320 << 20) / (2 * (3 * sizeof(double) + 9 * sizeof(Stored<PM>))));
+    if (PM != SDUGKS_FP32NEQ && (seg & 1) && m.nc <= most)
         March<PM, true>(m, cg, s, lagged, i0, w, j0, j1, ring, bcs, lx).run();
     else
         March<PM, false>(m, cg, s, lagged, i0, w, j0, j1, ring, bcs, lx).run();
