@@ -552,7 +552,7 @@ int sdugks_create(const sdugks_mesh *mesh, const sdugks_bc *bc, int32_t n_bc, co
             return cleanup(fail(SDUGKS_EHIP, "upload of the structured-grid tables failed"));
         h->dc.nx = mb.nx; h->dc.ny = mb.ny;
         h->dc.per_x = mb.per_x; h->dc.per_y = mb.per_y;
-        const CartPlan plan = plan_cart({h->dc}, h->precision);
+        const CartPlan plan = plan_cart({h->dc}, (int32_t)mb.bcs.size(), h->precision);
         cart_cut(h->dc, plan.rows);
         if (plan.threads) {
             h->blk = cart_block(h->dc, plan.threads, plan.K);
@@ -1011,9 +1011,13 @@ int batch_build_tables(sdugks_batch_t *b)
     for (int mode = 0; mode < 3; mode++)
         for (int k = 0; k < 2; k++) {
             std::vector<DevCart> cs;
+            size_t n_bc = 0;
             for (sdugks_t *h : b->members)
-                if (h->mb.cart && h->precision == mode && narrow(h) == (k == 1)) cs.push_back(h->dc);
-            if (!cs.empty()) plans[mode][k] = plan_cart(cs, mode);
+                if (h->mb.cart && h->precision == mode && narrow(h) == (k == 1)) {
+                    cs.push_back(h->dc);
+                    n_bc = std::max(n_bc, h->mb.bcs.size());
+                }
+            if (!cs.empty()) plans[mode][k] = plan_cart(cs, (int32_t)n_bc, mode);
         }
     std::vector<BatchGroup> want;
     for (size_t k = 0; k < b->members.size(); k++) {

@@ -29,11 +29,11 @@ inline CartTimes cart_times(int precision)
 constexpr int64_t kSimds = 1024;
 constexpr int32_t kWholeSteps = 1000;   // steps per launch of a mesh in one box, at most
 
-// Time of `waves` equal waves, `most` at a time on a SIMD, which take one + time[k]
-// times `units` with k + 1 of them on it.
-inline double cart_rounds(int64_t waves, int32_t most, double one, const double *time, double units)
+// Time of `waves` equal waves, `at_once` of them on the chip, which take one + time[k]
+// times `units` with up to k + 1 of them on a SIMD.
+inline double cart_rounds(int64_t waves, int64_t at_once, double one, const double *time, double units)
 {
-    const int64_t full = waves / (most * kSimds), rest = (waves % (most * kSimds) + kSimds - 1) / kSimds;
+    const int64_t most = (at_once + kSimds - 1) / kSimds, full = waves / at_once, rest = (waves % at_once + kSimds - 1) / kSimds;
     return (double)full * (one + units * time[most - 1]) + (rest > 0 ? one + units * time[rest - 1] : 0.0);
 }
 
@@ -66,21 +66,28 @@ inline void cart_cut(DevCart &c, int32_t rows)
 // The march over all members: segments of nearly `rows` rows each, such that
 // the waves fill the SIMDs in whole rounds and are not much longer than their
 // start (about three rows' time: the two rows before and after a segment take
-// part of a row's work).  Long segments read few rows twice.
-inline CartPlan plan_march(const std::vector<DevCart> &members, int precision)
+// part of a row's work).  Long segments read few rows twice, but at a wall their
+// boundary states take LDS: in FP64 eight waves of 23 rows fit a CU and seven of 38
+// (2048 x 2048 cells: one round of 38 rows was planned, and took two).  Times are
+// those of a state that the memory-side cache holds; a larger one is bound by memory
+// whatever the cut, 2048 x 2048 cells by a factor of 2 in FP64 and 1.3 in FP32 deviations.
+inline CartPlan plan_march(const std::vector<DevCart> &members, int32_t n_bc, int precision)
 {
     const CartTimes t = cart_times(precision);
     CartPlan best;
     for (int32_t rows = 1; rows <= 64; rows++) {
         int64_t waves = 0;
         int32_t longest = 0;
+        size_t lds = 0;
         for (const DevCart &m : members) {
             DevCart c = m;
             cart_cut(c, rows);
             waves += (int64_t)c.strips * c.segs;
             longest = std::max(longest, (c.ny + c.segs - 1) / c.segs);
+            lds = std::max(lds, march_lds_bytes(c, n_bc, precision));
         }
-        const double us = t.launch + cart_rounds(waves, 2, 0.0, t.row, longest + 3.0);
+        const int64_t at_once = (int64_t)march_waves_per_cu(march_ring_bytes(precision) + lds) * (kSimds / 4);
+        const double us = t.launch + cart_rounds(waves, at_once, 0.0, t.row, longest + 3.0);
         if (best.rows == 0 || us < best.us) best = {rows, 0, 0, us};
     }
     return best;
@@ -116,10 +123,10 @@ inline CartBlock cart_block(const DevCart &c, int32_t threads, int32_t K)
 }
 
 // Boxes over all members, or the march where that takes less time.
-inline CartPlan plan_cart(const std::vector<DevCart> &members, int precision)
+inline CartPlan plan_cart(const std::vector<DevCart> &members, int32_t n_bc, int precision)
 {
     const CartTimes t = cart_times(precision);
-    CartPlan best = plan_march(members, precision);
+    CartPlan best = plan_march(members, n_bc, precision);
     for (int32_t threads : {128, 256, 512})
         for (int32_t K : {1, 2, 3, 4, 5, 6, 32}) {      // 32: only where every mesh fits one box
             int64_t boxes = 0;
@@ -132,8 +139,8 @@ inline CartPlan plan_cart(const std::vector<DevCart> &members, int precision)
             if (!fits) continue;
             // a workgroup of eight waves takes two on each of a CU's SIMDs, and a CU holds one,
             // with nothing beside it while it loads
-            const double us = (t.box_launch + (threads == 512 ? cart_rounds((boxes + 255) / 256 * 256 * 8, 2, t.round + 0.6, t.step, K)
-                                                              : cart_rounds(boxes * (threads / 64), t.waves, t.round, t.step, K))) / K;
+            const double us = (t.box_launch + (threads == 512 ? cart_rounds((boxes + 255) / 256 * 256 * 8, 2 * kSimds, t.round + 0.6, t.step, K)
+                                                              : cart_rounds(boxes * (threads / 64), t.waves * kSimds, t.round, t.step, K))) / K;
             if (us < best.us) best = {best.rows, threads, K, us};
         }
     return best;

@@ -231,7 +231,28 @@ inline bool block_wraps(const DevCart &c, const CartBlock &B)
 // which all wrap rows inside a box or all do not.
 hipError_t launch_step_batch_block(const BatchTable &tab, bool wrap, int threads, int mode, int steps, int parity,
                                    int cap_tiles, size_t lds, hipStream_t st, GraphChain *gc = nullptr);
-size_t march_lds_bytes(const DevCart &c, int n_bc, int mode);   // besides the march's static LDS
+// LDS of a wave of the march: W and f of its last kRing rows, and besides (the
+// launch's dynamic LDS) the boundary table and nine values for each row of a segment
+// and the two on either side of it, for both columns outside the walls where
+// one strip holds both.
+constexpr int kRing = 3;
+constexpr size_t kBcBytes = 4 * sizeof(double);
+constexpr size_t march_ring_bytes(int mode)
+{
+    return (size_t)kRing * 64 * (3 * sizeof(double) + 9 * (mode == SDUGKS_FP64 ? sizeof(double) : sizeof(float)));
+}
+inline size_t march_lds_bytes(const DevCart &c, int n_bc, int mode)
+{
+    const size_t rows = c.seg_h + (c.seg_more > 0) + 4, value = mode == SDUGKS_FP32DEV ? sizeof(float) : sizeof(double);
+    return n_bc * kBcBytes + (c.per_x ? 0 : (c.strips == 1 ? 2 : 1) * rows * 9 * value);
+}
+// Waves of the march on a CU at once: two on each of its four SIMDs, the most that
+// the registers allow, where the LDS (160 KB, allocated in units of 1280 bytes) holds them.
+inline int march_waves_per_cu(size_t lds)
+{
+    const int fit = (int)(160 * 1024 / ((lds + 1279) / 1280 * 1280));
+    return fit < 8 ? (fit < 1 ? 1 : fit) : 8;
+}
 // Workgroups of a structured instance cut into strips and segments.
 inline int32_t cart_groups(const DevCart &c) { return c.strips * c.segs; }
 hipError_t launch_step_batch_cart(const BatchTable &tab, int mode, int parity, int cap_tiles, size_t lds,

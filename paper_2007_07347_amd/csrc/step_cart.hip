@@ -118,12 +118,14 @@ __device__ __forceinline__ Side<R> shift(const Side<R> &v)
     return {{shift<CTRL>(v.c[0]), shift<CTRL>(v.c[1]), shift<CTRL>(v.c[2])}, shift<CTRL>(v.s), shift<CTRL>(v.d)};
 }
 
-constexpr int kRing = 3;
 template <int PM>
 struct Ring {
     double W[kRing][3][64];
     Stored<PM> f[kRing][9][64];
 };
+static_assert(sizeof(Ring<SDUGKS_FP64>) == march_ring_bytes(SDUGKS_FP64) &&
+                  sizeof(Ring<SDUGKS_FP32DEV>) == march_ring_bytes(SDUGKS_FP32DEV) && sizeof(WallBC) == kBcBytes,
+              "the march's LDS as the planner counts it");
 
 // One time step of rows [j0, j1) of the columns [i0, i0 + w), w <= 60, by one
 // wave, from the lowest row up or (DOWN) from the highest down.  Where
@@ -496,14 +498,6 @@ __global__ void __launch_bounds__(64, 2) k_step_batch_cart(BatchTable tab, int p
 }
 
 }  // namespace
-
-// Boundary entries, and nine values for each row of a segment and the two on either side of it,
-// for both columns outside the walls where one strip holds both.
-size_t march_lds_bytes(const DevCart &c, int n_bc, int mode)
-{
-    const size_t rows = c.seg_h + (c.seg_more > 0) + 4, value = mode == SDUGKS_FP32DEV ? sizeof(float) : sizeof(double);
-    return n_bc * sizeof(WallBC) + (c.per_x ? 0 : (c.strips == 1 ? 2 : 1) * rows * 9 * value);
-}
 
 hipError_t launch_step_cart(const DevMesh &m, const DevCart &c, const DevState &s, int lagged, int mode,
                             hipStream_t st, GraphChain *gc)
