@@ -75,15 +75,14 @@ __device__ __forceinline__ void feq9(double rho, double mx, double my, double ux
 }
 
 // 1 / x for a density (a positive normal number): the hardware's approximation,
-// to some 2^-24, and three Newton steps.  The second leaves an error far below an
-// ulp, which still misses the nearest number just below a power of two (1 - 3 2^-53);
-// the residual of the third is exact, and the result is that of a division at
-// every density tried, at half its cost (the third step takes 0 to 1 % of a step).
+// off by some 2^-24 = e; one step to e^3, and a last one by its residual, which is
+// exact.  The result is that of a division at every density tried, at half its
+// cost; without the last step it misses the nearest number just below a power of
+// two (1 - 3 2^-53).
 __device__ __forceinline__ double recip(double x)
 {
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma_(fma_(-x, y, 1.0), y, y);
-    y = fma_(fma_(-x, y, 1.0), y, y);
+    const double y0 = __builtin_amdgcn_rcp(x), e = fma_(-x, y0, 1.0);
+    const double y = fma_(y0, fma_(e, e, e), y0);
     return fma_(fma_(-x, y, 1.0), y, y);
 }
 
