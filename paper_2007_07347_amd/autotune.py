@@ -74,40 +74,51 @@ def _store_cache(path, db):
         pass
 
 
-def time_candidate(mesh, bcs, sched, steps=200, warmup=20, **kw):
+def _time(mesh, bcs, sched, steps, warmup, timed, kw):
+    """(ms per step, threads per workgroup that ran) of a candidate; launches
+    alike (timed: those before) are timed once, as the library's choice of
+    threads and the same number asked for."""
     import torch
     s = sdugks.Solver(mesh, bcs, **sched, **kw)
-    s.step(warmup)
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    a.record(s.stream)
-    s.step(steps)
-    b.record(s.stream)
-    b.synchronize()
-    ms = a.elapsed_time(b) / steps
+    how = s.schedule()
+    key = (sched.get("tile_cells"), *how.values())
+    if key not in timed:
+        s.step(warmup)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(s.stream)
+        s.step(steps)
+        b.record(s.stream)
+        b.synchronize()
+        timed[key] = a.elapsed_time(b) / steps
     s.close()
-    return ms
+    return timed[key], how["threads"]
+
+
+def time_candidate(mesh, bcs, sched, steps=200, warmup=20, **kw):
+    return _time(mesh, bcs, sched, steps, warmup, {}, kw)[0]
 
 
 def autotune(mesh, bcs, candidates=None, steps=200, cache=CACHE, refresh=False, **kw):
     """Return ({"tile_cells", "block_threads"}, table) for the fastest fused
-    schedule of this mesh; table lists ms per step of every candidate."""
+    schedule of this mesh; table lists ms per step of every candidate and the
+    threads per workgroup that ran."""
     key = signature(mesh, kw.get("precision", sdugks.FP64))
     db = _load_cache(cache) if cache else {}
     if not refresh and key in db:
         return db[key]["best"], db[key]["table"]
-    table = []
+    table, timed = [], {}
     for sched in candidates_for([(mesh, bcs, kw)], candidates):
         try:
-            ms = time_candidate(mesh, bcs, sched, steps=steps, **kw)
+            ms, threads = _time(mesh, bcs, sched, steps, 20, timed, kw)
         except sdugks.SdugksError as e:        # e.g. a tile too small for the mesh degree
             table.append({**sched, "ms": None, "error": str(e)})
             continue
-        table.append({**sched, "ms": ms})
+        table.append({**sched, "ms": ms, "threads": threads})
     ok = [r for r in table if r["ms"] is not None]
     if not ok:
         raise RuntimeError("no candidate schedule fits: " + "; ".join(r["error"] for r in table))
     best = min(ok, key=lambda r: r["ms"])
-    best = {k: v for k, v in best.items() if k not in ("ms", "error")}
+    best = {k: v for k, v in best.items() if k not in ("ms", "error", "threads")}
     if cache:
         db[key] = {"best": best, "table": table}
         _store_cache(cache, db)
@@ -169,7 +180,7 @@ def autotune_batch(problems, candidates=None, steps=50, cache=CACHE, refresh=Fal
     if not ok:
         raise RuntimeError("no candidate schedule fits: " + "; ".join(r["error"] for r in table))
     best = min(ok, key=lambda r: r["ms"])
-    best = {k: v for k, v in best.items() if k not in ("ms", "error")}
+    best = {k: v for k, v in best.items() if k not in ("ms", "error", "threads")}
     if cache:
         db[key] = {"best": best, "table": table}
         _store_cache(cache, db)

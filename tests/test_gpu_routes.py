@@ -198,3 +198,17 @@ def test_profiled_steps_are_launched_as_steps_are(sd):
     s.close()
     print(together, each, flush=True)
     assert together < 0.75 * each
+
+
+def test_autotuner_reports_the_threads_that_ran(sd):
+    """Every candidate runs on the threads it names; the library's choice (0) is
+    reported as what it is, and where that is the launch of another candidate
+    (up to 768 tiles: 256 threads) both have the one time."""
+    from paper_2007_07347_amd import autotune
+    mesh, bcs = meshgen.cylinder_ogrid(60, 20, seed=1)
+    best, table = autotune.autotune(mesh, bcs, steps=20, cache=None, nu=2e-3, cfl=0.5)
+    rows = {(r["tile_cells"], r["block_threads"]): r for r in table}
+    assert set(rows) == set(autotune.CANDIDATES)
+    assert all(r["threads"] == bt for (_, bt), r in rows.items() if bt)
+    assert rows[64, 0]["threads"] == 256 and rows[64, 0]["ms"] == rows[64, 256]["ms"]
+    assert set(best) == {"tile_cells", "block_threads", "structured"}
