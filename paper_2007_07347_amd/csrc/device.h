@@ -201,15 +201,15 @@ inline bool step_tiled_fits(const DevTiles &t, int block)
 }
 // Threads of the fused step where the caller leaves them to the library: four
 // waves a tile while all tiles are on the chip at once (three per CU in FP64:
-// a 45,000-cell mesh takes 8.0 us a step, with two waves 8.3), two beyond (a
-// 200,000-cell mesh with FP32 deviations takes 13.4 us, with four waves 17.1).
+// a 45,000-cell mesh took 8.0 us a step where two waves took 8.3), two beyond (a
+// 200,000-cell mesh with FP32 deviations takes 13.6 us, with four waves 17.1).
 inline int step_tiled_block(const DevTiles &t, int64_t n_tiles)
 {
     return n_tiles <= 768 && !step_tiled_two(t, 256) ? 256 : 128;
 }
 // Threads per tile of a workgroup whose threads the caller gives: half of them,
 // and two tiles at a time, beyond as many tiles as the chip takes at once, where
-// half the waves do more with a tile (one or two tiles: see k_step_tiled)
+// half the waves do more with a tile (figures: Place in step_tiled.hip).
 inline int step_tiled_per(const DevTiles &t, int block, int64_t n_tiles)
 {
     return block > 64 && n_tiles > 768 * 256 / block && step_tiled_fits(t, block / 2) ? block / 2 : block;

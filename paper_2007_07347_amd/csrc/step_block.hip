@@ -18,7 +18,7 @@
 // What bounds it is the latency of a step's chain (three barriers, wave shifts,
 // one cell per lane).  us per step against one workgroup per tile and launch:
 // 4 x 32 cells FP64 6.9 -> 2.2, 48 x 48 FP64 8.0 -> 3.2, 101 x 101 FP32
-// deviations 8.1 -> 3.4, 256 x 256 10.3 -> 6.2, FP64 10.8 -> 7.1.  With the march
+// deviations 8.1 -> 3.4, 256 x 256 10.3 -> 6.3, FP64 10.8 -> 7.3.  With the march
 // instead 256 x 256 takes 9.7 and 10.6; 512 x 512 15.3 against 16.3 (FP32
 // deviations), where the two meet.
 #include <cstdint>

@@ -36,7 +36,8 @@
 // ahead, or cache lines touched before they are requested change nothing or cost
 // 5 to 20 %; so do non-temporal stores.  Before it, one workgroup per 16 x 14 or
 // 16 x 7 cells with their halo in LDS: 52.8 and 86.7 us, 1430 lane instructions
-// per cell against 550; now 30.9 and 44.4.
+// per cell against 550; now 31.5 and 44.7 (2048 x 2048 cells 129 and 227, FP64 reading
+// and writing 1.04 GB at 4.6 TB/s).
 #include <cstdint>
 #include <type_traits>
 #include <utility>
@@ -459,9 +460,9 @@ __device__ __forceinline__ void march_unit(const DevMesh &m, const DevCart &cg, 
     // Every other segment downwards while the state, in and out, is little more than
     // the memory-side cache's 256 MB.  us a step, upwards all against every other
     // downwards, by cells an edge: FP64 800 32.3 / 29.2, 1024 45.7 / 43.3, 1152 53.3 /
-    // 51.0, 1280 (315 MB) 77.6 / 77.3, 1448 (403 MB) 100 / 105; FP32 deviations 1024 31.3 / 30.7, 1448 (252 MB) 50.1 / 50.1, 1600 76.0 / 76.0,
-    // 1792 (385 MB) 95.7 / 97.4, 2560 199 / 200; FP32NEQ the same up to 1024 and 2 to 8 %
-    // slower beyond.
+    // 51.0, 1280 (315 MB) 77.6 / 77.3, 1448 (403 MB) 100 / 105; FP32 deviations 1024 31.3 /
+    // 30.7, 1448 (252 MB) 50.1 / 50.1, 1600 76.0 / 76.0, 1792 (385 MB) 95.7 / 97.4, 2560 199 /
+    // 200; FP32NEQ the same up to 1024 and 2 to 8 % slower beyond.
     constexpr int most = (int)(((size_t)320 << 20) / (2 * (3 * sizeof(double) + 9 * sizeof(Stored<PM>))));
     if (PM != SDUGKS_FP32NEQ && (seg & 1) && m.nc <= most)
         March<PM, true>(m, cg, s, lagged, i0, w, j0, j1, ring, bcs, lx).run();

@@ -50,8 +50,9 @@
 // loads, three barriers, the phases), 5 to 6 us besides the launch; beyond,
 // instruction issue and the tables' bytes.  Against four lanes per cell that
 // evaluated each face from both of its cells: 200,000 triangles in FP32
-// deviations 18.9 -> 13.4 us a step, 45,000 cells of a hybrid mesh in FP64
-// 9.4 -> 8.4; tighter register limits that spill took 22 to 38 us.
+// deviations 19.1 -> 13.6 us a step, 45,000 cells of a hybrid mesh in FP64
+// 9.8 -> 8.1; tighter register limits that spill took 22 to 38 us.  fbar+ carried
+// back in phase 2 rather than one offset per face: 13.6 and 8.7.
 #include <type_traits>
 #include <utility>
 
